@@ -56,6 +56,21 @@ __device__ __forceinline__ float vgpr_copy(float x) {
   return v;
 }
 
+// An empty asm statement that "modifies" a loaded value: the wait for the
+// load is placed here, and no later use of the value can need one.
+template <typename X>
+__device__ __forceinline__ void in_register(X& x) {
+  if constexpr (sizeof(X) == 4) {
+    uint32_t w = __builtin_bit_cast(uint32_t, x);
+    asm volatile("" : "+v"(w));
+    x = __builtin_bit_cast(X, w);
+  } else {
+    uint32_t w = x;
+    asm volatile("" : "+v"(w));
+    x = (X)w;
+  }
+}
+
 // Exact three-way minimum (one v_min3_f32).  Inputs are never NaN here: DP
 // values start at 0 or +inf and every LDS slot a lane reads before its
 // first tile is initialised (+inf boundaries, a zeroed reference ring).

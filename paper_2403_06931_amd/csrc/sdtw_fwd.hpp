@@ -72,11 +72,8 @@ struct FwdParams {
   float prune_tau;          // pruning threshold of the kPruned cost kind
 };
 
-constexpr int kStepsPerBarrier = 8;
-
 template <int R, int T, int W, int KS, int XL>
 struct FwdShape {
-  static_assert(KS % 2 == 0, "the step loop is unrolled by two");
   static constexpr int KSTEP = KS;
   // lane -> lane exchange: XL = 1 through LDS slots, XL = 0 through a DPP
   // wave_shr:1 move; either way lane l+1 lags lane l by one step (a slot is
@@ -92,19 +89,72 @@ struct FwdShape {
   // two intervals ahead
   static constexpr int SPAN = LL * kWave * W + (W - 1) * LAG + 3 * KS + 2;
   static constexpr int SR = pow2_ceil<SPAN>();                // reference ring, tiles
+  // Steps unrolled together: their LDS addresses are one base per group plus
+  // constants.  The first UNROLL tiles of the reference ring are stored a
+  // second time behind its end, so that a lane's reads run past the wrap.
+  // (Fewer steps for tiles of many cells, whose per-step share of the
+  // addressing is small, to bound the code size.)
+  static constexpr int UNROLL = R * T >= 64 ? 4 : 8;
+  static_assert(KS % UNROLL == 0, "a barrier interval holds whole step groups");
   static constexpr int THREADS = kWave * W;
   static constexpr int ROWS = kWave * R * W;                  // rows per pass
   static constexpr int CHUNK = KS * T;                        // floats staged per interval
-  static constexpr int SLOTS = XL ? W * kWave * T : 0;        // lane -> lane slots
+  // LDS layout of tile rows: column t of tile slot x sits at
+  // (t / 4) * stride + 4 x + t % 4, so that the 16-byte accesses of
+  // neighbouring lanes (neighbouring tiles or slots) are contiguous and free
+  // of bank conflicts; with whole tiles side by side they were not (41 % of
+  // the LDS cycles of the 4- and 8-row tiles with LDS exchange).
+  static constexpr int REFP = (SR + UNROLL) * 4;              // plane stride, reference ring
+  // plane stride of the handoff rings and the lane -> lane slots (the same,
+  // as one instruction reads a slot in some lanes and a ring in another)
+  static constexpr int HANDP = XL && SH * 4 < kWave * 4 ? kWave * 4 : SH * 4;
+  static constexpr int HAND = HANDP * (T / 4);                // floats per handoff ring
+  static constexpr int SLOTS = XL ? W * HAND : 0;             // lane -> lane slots
   static constexpr int OUTBUF = KS * T;                       // row N over one interval
   // R = 8: the row checkpoint in the middle of each wavefront, one ring per
   // wavefront like the handoff rings
   // (checkpointing kernels only, after the other buffers)
   static constexpr int MIDRING = R * kWave > kRowCkpt ? W * SH * T : 0;
-  static constexpr int LDS_FLOATS = SR * T + W * SH * T + SLOTS + OUTBUF;
+  // (the same for every R: a tail pass of fewer rows per lane and more steps
+  // per group uses the memory of the kernel's own shape)
+  static constexpr int REFRING = (SR + 8) * T;
+  static_assert(UNROLL <= 8, "mirrored tiles");
+  static constexpr int LDS_FLOATS = REFRING + W * HAND + SLOTS + OUTBUF;
   template <bool CKPT>
   static constexpr int lds_floats() { return LDS_FLOATS + (CKPT ? MIDRING : 0); }
 };
+
+// One tile row of T lane values between registers and LDS, four at a time,
+// in planes of four columns STRIDE words apart (4 for a row stored in one
+// piece); every piece is 16-byte aligned.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <int STRIDE>
+__device__ __forceinline__ int plane_at(int x, int t) {
+  return (t >> 2) * STRIDE + 4 * x + (t & 3);
+}
+
+template <int T, int STRIDE, typename V>
+__device__ __forceinline__ void tile_load(V (&dst)[T], const V* src) {
+  static_assert(T % 4 == 0 && sizeof(V) == 4, "16-byte pieces");
+#pragma unroll
+  for (int t = 0; t < T; t += 4) {
+    const u32x4 w = *reinterpret_cast<const u32x4*>(src + (t / 4) * STRIDE);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) dst[t + u] = __builtin_bit_cast(V, (uint32_t)w[u]);
+  }
+}
+
+template <int T, int STRIDE, typename V>
+__device__ __forceinline__ void tile_store(V* dst, const V (&src)[T]) {
+#pragma unroll
+  for (int t = 0; t < T; t += 4) {
+    u32x4 w;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) w[u] = __builtin_bit_cast(uint32_t, src[t + u]);
+    *reinterpret_cast<u32x4*>(dst + (t / 4) * STRIDE) = w;
+  }
+}
 
 // Stage the reference tiles [tile0, tile0 + KS) and the wave-0 top boundary
 // (zeros on the first pass, the previous pass's last row after it) from
@@ -136,14 +186,27 @@ struct Stager {
     }
   }
 
-  __device__ __forceinline__ void commit(V* s_ref, V* s_hand0, int tile0, int tid) const {
+  __device__ __forceinline__ void commit(V* s_ref, V* s_hand0, int tile0, int tid) {
+    // every lane waits for its loads here, outside the branches below: a
+    // load that a branch leaves pending would make the next interval's first
+    // instruction wait for every store issued in between
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      in_register(ref[u]);
+      in_register(top[u]);
+    }
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int e = tid + u * S::THREADS;
       if (e < S::CHUNK) {
-        const int j = tile0 * T + e;
-        s_ref[j & (S::SR * T - 1)] = Val<V>::ref(ref[u]);
-        s_hand0[j & (S::SH * T - 1)] = top[u];
+        const int x = tile0 + e / T;
+        const int t = e % T;
+        const int at = plane_at<S::REFP>(x & (S::SR - 1), t);
+        s_ref[at] = Val<V>::ref(ref[u]);
+        // (chunks start at multiples of KS tiles: uniform)
+        if ((tile0 & (S::SR - 1)) == 0 && e < S::UNROLL * T)
+          s_ref[at + 4 * S::SR] = Val<V>::ref(ref[u]);
+        s_hand0[plane_at<S::HANDP>(x & (S::SH - 1), t)] = top[u];
       }
     }
   }
@@ -258,10 +321,10 @@ __device__ __forceinline__ void ckpt_flush(const FwdParams& p, LaneState<R, T>& 
 // of its own (rowck_mid_put, rowck_mid_copy).  Checkpoint stores are non-temporal: the
 // backward reads a fraction of them, later, and they should not leave the
 // caches full of dirty lines.
-template <int T, int KS, int SH>
+template <int T, int KS, int SH, int HANDP>
 __device__ __forceinline__ void rowck_copy(const FwdParams& p, const PassGeom& G,
                                            const float* s_hand, int it) {
-  const float* ring = s_hand + G.wave * SH * T;
+  const float* ring = s_hand + G.wave * HANDP * (T / 4);
   const int tau0 = it * KS - G.lane0_delay;
 #pragma unroll
   for (int e0 = 0; e0 < KS * T; e0 += kWave) {
@@ -270,7 +333,7 @@ __device__ __forceinline__ void rowck_copy(const FwdParams& p, const PassGeom& G
       const int tau = tau0 + e / T;
       const int col = tau * T + (e & (T - 1));
       if (tau >= 0 && col < p.ref_len) {
-        const float v = ring[(tau & (SH - 1)) * T + (e & (T - 1))];
+        const float v = ring[plane_at<HANDP>(tau & (SH - 1), e & (T - 1))];
         __builtin_nontemporal_store(v, &G.rowck[col]);
       }
     }
@@ -316,30 +379,18 @@ __device__ __forceinline__ void rowck_mid_copy(const FwdParams& p, const PassGeo
 
 // One step: the R x T block of this lane's current tile.  OUTK >= 0 marks
 // the wavefront holding the row to store and that row's register index.
-// `top` is the block's top boundary: the previous lane's bottom row over this
-// tile (for lane 0, the previous wave's, or the top boundary of the pass).
+// `up` is the block's top boundary: the previous lane's bottom row (lane 0:
+// this wave's handoff ring), read from LDS with XL, else shifted from the
+// previous lane's registers.  `hout` (XL) is where the bottom row goes: this lane's slot, or for
+// lane 63 the next wave's handoff ring.  The stored row's values are left in
+// L.bot if it is the lane's last row, else in `outv` (step_stores).
 template <int R, int T, int W, int KS, int XL, int KIND, int CKM, int OUTK, typename V>
 __device__ __forceinline__ void fwd_step(const FwdParams& p, LaneState<R, T, V>& L,
-                                         const PassGeom& G, const V (&rv)[T],
-                                         const V (&top)[T], int g, V* s_hand, V* s_slot) {
+                                         const PassGeom& G, const V (&rv)[T], V (&up)[T], int g,
+                                         V* hout, V (&outv)[T]) {
   using S = FwdShape<R, T, W, KS, XL>;
-  V up[T];
-  if constexpr (XL) {
-    // lane l-1's slot, written at the end of step g-1 (lane 0: this wave's
-    // handoff ring); the read's latency is covered by the block's
-    // subtractions and products, which do not depend on it
-    const V* hin = s_hand + G.wave * S::SH * T + ((g - G.lane0_delay) & (S::SH - 1)) * T;
-    const V* tin = G.lane != 0 ? s_slot + (G.wave * kWave + G.lane - 1) * T : hin;
-#pragma unroll
-    for (int t = 0; t < T; ++t) up[t] = tin[t];
-  } else {
-#pragma unroll
-    for (int t = 0; t < T; ++t) up[t] = Val<V>::shr1(top[t], L.bot[t]);
-  }
   V upleft = L.corner;                          // D(row-1, first col - 1)
   L.corner = up[T - 1];
-  const int tau_out = g - G.out_delay;
-  const bool do_out = OUTK >= 0 && tau_out >= 0 && tau_out < G.ntiles;
   if constexpr (Val<V>::kAntiDiagonal) {
     // Anti-diagonal order (packed binary16): gfx950 needs a wait state
     // between dependent packed instructions; cells (k, t) and (k+1, t-1)
@@ -357,12 +408,9 @@ __device__ __forceinline__ void fwd_step(const FwdParams& p, LaneState<R, T, V>&
         D[k][t] = Val<V>::template cell<KIND>(L.qv[k], rv[t], u, lf, dg, L.tau);
       }
     }
-    if constexpr (OUTK >= 0) {
-      if (do_out && G.lane == G.out_lane) {
-        V* dst = reinterpret_cast<V*>(G.s_out) + (g & (KS - 1)) * T;
+    if constexpr (OUTK >= 0 && OUTK < R - 1) {
 #pragma unroll
-        for (int t = 0; t < T; ++t) dst[t] = D[OUTK][t];
-      }
+      for (int t = 0; t < T; ++t) outv[t] = D[OUTK][t];
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) L.dl[k] = D[k][T - 1];
@@ -384,15 +432,9 @@ __device__ __forceinline__ void fwd_step(const FwdParams& p, LaneState<R, T, V>&
     }
     upleft = L.dl[k];
     L.dl[k] = cur[T - 1];
-    if (OUTK == k) {                            // folded once the k loop is unrolled
-      if (do_out && G.lane == G.out_lane) {
-        // to LDS only: at the interval's end the wave folds it (row N) or
-        // copies it to the row buffer (keeping a global store out of the
-        // step, whose LDS waits would otherwise cover it)
-        V* dst = reinterpret_cast<V*>(G.s_out) + (g & (KS - 1)) * T;
+    if (OUTK == k && k < R - 1) {               // folded once the k loop is unrolled
 #pragma unroll
-        for (int t = 0; t < T; ++t) dst[t] = cur[t];
-      }
+      for (int t = 0; t < T; ++t) outv[t] = cur[t];
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) up[t] = cur[t];
@@ -402,22 +444,15 @@ __device__ __forceinline__ void fwd_step(const FwdParams& p, LaneState<R, T, V>&
   for (int t = 0; t < T; ++t) L.bot[t] = up[t];
 
   if constexpr (XL) {
-    // the bottom row feeds lane l+1 (its slot is read at the start of the
-    // next step, before this lane overwrites it at the end of that step).
-    // LDS operations of one wavefront complete in order; the compiler must
-    // not move the next step's slot read (another lane's slot, so no alias
-    // in one thread's view) above this store.
-    V* sout = s_slot + (G.wave * kWave + G.lane) * T;
-#pragma unroll
-    for (int t = 0; t < T; ++t) sout[t] = L.bot[t];
+    // The bottom row feeds lane l+1 (its slot is read at the start of the
+    // next step, before this lane overwrites it at the end of that step);
+    // lane 63's goes to the next wave's handoff ring with the same store (to
+    // its own slot in the wave that holds the stored row, which has no wave
+    // with rows after it).  LDS operations of one wavefront complete in
+    // order; the compiler must not move the next step's slot read (another
+    // lane's slot, so no alias in one thread's view) above this store.
+    tile_store<T, S::HANDP>(hout, L.bot);
     asm volatile("" ::: "memory");
-  }
-
-  // lane 63 hands its bottom row to the next wave
-  if (G.wave + 1 < W && G.lane == kWave - 1) {
-    V* hout = s_hand + (G.wave + 1) * S::SH * T + ((g - G.lane63_delay) & (S::SH - 1)) * T;
-#pragma unroll
-    for (int t = 0; t < T; ++t) hout[t] = L.bot[t];
   }
 
   // Checkpoint column kc*ckpt_every - 1 is the last column of tile kc*tpc - 1
@@ -434,19 +469,125 @@ __device__ __forceinline__ void fwd_step(const FwdParams& p, LaneState<R, T, V>&
     rowck_mid_put<R, T, FwdShape<R, T, W, KS, XL>::SH>(G, L.bot, g);
 }
 
-// LDS inputs of step g, read one step ahead: this lane's reference tile and,
-// without XL, the handoff ring's top boundary (fwd_step shifts the bottom
-// rows to the other lanes); with XL, fwd_step reads the top boundary itself.
+// LDS addresses of a group of UNROLL steps from step g on: the lane's first
+// reference tile (the following ones run on, over the mirrored end of the
+// ring), the first tile of this wave's handoff ring and the slots lane 63's
+// tiles go to (delays and ring sizes are multiples of UNROLL tiles, so only
+// the last of those can wrap).
+template <typename V>
+struct GroupPtrs {
+  const V* ref;
+  const V* top;
+  V* hand;
+  V* hand_last;
+};
+
 template <int R, int T, int W, int KS, int XL, typename V>
-__device__ __forceinline__ void step_inputs(V (&rv)[T], V (&top)[T], int g, const PassGeom& G,
-                                            const V* s_ref, const V* s_hand, const V* s_slot) {
+__device__ __forceinline__ GroupPtrs<V> group_ptrs(int g, const PassGeom& G, const V* s_ref,
+                                                   V* s_hand) {
   using S = FwdShape<R, T, W, KS, XL>;
-  const V* rin = s_ref + ((g - G.my_delay) & (S::SR - 1)) * T;
-  const V* hin = s_hand + G.wave * S::SH * T + ((g - G.lane0_delay) & (S::SH - 1)) * T;
+  static_assert(S::LAG % S::UNROLL == 0 && kWave % S::UNROLL == 0, "aligned handoff rings");
+  const int a = g - G.lane0_delay;                     // a multiple of UNROLL
+  const int x = a - (kWave - 1);
+  V* next = s_hand + (G.wave + 1) * S::HAND;           // (not written by the last wave)
+  return GroupPtrs<V>{s_ref + ((g - G.my_delay) & (S::SR - 1)) * 4,
+                      s_hand + G.wave * S::HAND + (a & (S::SH - 1)) * 4,
+                      next + (x & (S::SH - 1)) * 4,
+                      next + ((x + S::UNROLL - 1) & (S::SH - 1)) * 4};
+}
+
+// The stores of a step that only one lane makes: without XL, lane 63's
+// bottom row to the next wave's handoff ring (the wave that holds the stored
+// row has none after it with rows in this pass); in that wave, the stored
+// row's values over the tile to s_out (LDS only: at the interval's end the
+// wave folds them, or copies them to the row buffer, skipping tiles outside
+// the reference).  Without XL they are issued in the step after, once its
+// reads have arrived: the compiler cannot count a branch's stores, and with
+// them between a read and its use it waits for LDS operations that have just
+// been issued, in every step.
+template <int R, int T, int W, int KS, int XL, int OUTK, typename V>
+__device__ __forceinline__ void step_stores(const LaneState<R, T, V>& L, const PassGeom& G, int g,
+                                            V* hout, const V (&outv)[T]) {
+  using S = FwdShape<R, T, W, KS, XL>;
+  if constexpr (OUTK >= 0) {
+    if (G.lane == G.out_lane) {
+      V* dst = reinterpret_cast<V*>(G.s_out) + (g & (KS - 1)) * T;
+      if constexpr (OUTK < R - 1) {
+        tile_store<T, 4>(dst, outv);
+      } else {
+        tile_store<T, 4>(dst, L.bot);
+      }
+    }
+  } else if constexpr (!XL) {
+    if (G.lane == kWave - 1) tile_store<T, S::HANDP>(hout, L.bot);
+  }
+}
+
+// The KS steps of barrier interval `it`, in groups of UNROLL.  The reference
+// tile of a step (and, without XL, lane 0's top boundary) is read while the
+// step before it computes; the scheduling barrier keeps those reads ahead of
+// the step's arithmetic (left to itself the compiler sinks them to the end
+// of the step, which exposes the LDS latency in every step when few
+// wavefronts share a SIMD).
+template <int R, int T, int W, int KS, int XL, int KIND, int CKM, int OUTK, typename V>
+__device__ __forceinline__ void fwd_steps(const FwdParams& p, LaneState<R, T, V>& L,
+                                          const PassGeom& G, int it, V (&rv)[2][T],
+                                          V (&top)[2][T], GroupPtrs<V>& P, const V* s_ref,
+                                          V* s_hand, V* s_slot) {
+  using S = FwdShape<R, T, W, KS, XL>;
+  constexpr int U = S::UNROLL;
+#pragma unroll 1
+  for (int s0 = 0; s0 < KS; s0 += U) {
+    const int g0 = it * KS + s0;
+    const GroupPtrs<V> N = group_ptrs<R, T, W, KS, XL, V>(g0 + U, G, s_ref, s_hand);
+    // with XL: lane l-1's slot and this lane's; lane 0 reads and lane 63
+    // writes a handoff ring instead, one tile a step
+    V* slot = XL ? s_slot + G.wave * S::HAND + G.lane * 4 : nullptr;
+    const bool to_ring = OUTK < 0 && G.lane == kWave - 1;
+    const V* tin = XL && G.lane != 0 ? slot - 4 : P.top;
+    const int tstep = XL && G.lane != 0 ? 0 : 4;
+    V* tout = XL && !to_ring ? slot : P.hand;
+    V* tout_last = XL && !to_ring ? slot : P.hand_last;
+    const int ostep = XL && !to_ring ? 0 : 4;
+    V outv[T];
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    rv[t] = rin[t];
-    if constexpr (!XL) top[t] = hin[t];
+    for (int s = 0; s < U; ++s) {
+      V up[T];
+      if constexpr (XL) tile_load<T, S::HANDP>(up, tin + s * tstep);
+      tile_load<T, S::REFP>(rv[(s + 1) & 1], s + 1 < U ? P.ref + (s + 1) * 4 : N.ref);
+      if constexpr (!XL)
+        tile_load<T, S::HANDP>(top[(s + 1) & 1], s + 1 < U ? P.top + (s + 1) * 4 : N.top);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (XL) {
+        fwd_step<R, T, W, KS, XL, KIND, CKM, OUTK, V>(
+            p, L, G, rv[s & 1], up, g0 + s, s + 1 < U ? tout + s * ostep : tout_last, outv);
+        step_stores<R, T, W, KS, XL, OUTK, V>(L, G, g0 + s, nullptr, outv);
+      } else {
+        V(&u)[T] = top[s & 1];
+        // The DPP moves go out in one run at raised priority.  Two wavefronts
+        // of a SIMD issue a vector instruction each per quad-cycle while they
+        // stay in step; a DPP move cannot be paired, and moves of the two
+        // wavefronts that interleave with the other's arithmetic leave them
+        // out of step for tens of instructions.  512 x 2,000 vs 20,000 with
+        // (8,8,4,32) tiles: 1.99 ms without, 1.74 ms with the raised
+        // priority; 256 x 1,000 vs 50,000 with (2,16,8,16): 1.87 and 1.55 ms.
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(3);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < T; ++t) u[t] = Val<V>::shr1(u[t], L.bot[t]);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s > 0)
+          step_stores<R, T, W, KS, XL, OUTK, V>(L, G, g0 + s - 1, P.hand + (s - 1) * 4, outv);
+        fwd_step<R, T, W, KS, XL, KIND, CKM, OUTK, V>(p, L, G, rv[s & 1], u, g0 + s, nullptr,
+                                                      outv);
+      }
+    }
+    if constexpr (!XL)
+      step_stores<R, T, W, KS, XL, OUTK, V>(L, G, g0 + U - 1, P.hand_last, outv);
+    P = N;
   }
 }
 
@@ -488,32 +629,17 @@ __device__ __forceinline__ void out_copy(const PassGeom& G, int it) {
   }
 }
 
-// The KS steps of barrier interval `it`.  The reference tile of step g+1
-// (and, without XL, its handoff input) is read while step g computes (two
-// register sets, the step loop unrolled by two).
-template <int R, int T, int W, int KS, int XL, int KIND, int CKM, int OUTK, typename V>
-__device__ __forceinline__ void fwd_steps(const FwdParams& p, LaneState<R, T, V>& L,
-                                          const PassGeom& G, int it, V (&rvA)[T], V (&injA)[T],
-                                          V (&rvB)[T], V (&injB)[T], const V* s_ref, V* s_hand,
-                                          V* s_slot) {
-#pragma unroll 1
-  for (int s = 0; s < KS; s += 2) {
-    const int g = it * KS + s;
-    step_inputs<R, T, W, KS, XL>(rvB, injB, g + 1, G, s_ref, s_hand, s_slot);
-    fwd_step<R, T, W, KS, XL, KIND, CKM, OUTK, V>(p, L, G, rvA, injA, g, s_hand, s_slot);
-    step_inputs<R, T, W, KS, XL>(rvA, injA, g + 2, G, s_ref, s_hand, s_slot);
-    fwd_step<R, T, W, KS, XL, KIND, CKM, OUTK, V>(p, L, G, rvB, injB, g + 1, s_hand, s_slot);
-  }
-}
-
 // All barrier intervals of one pass.
 template <int R, int T, int W, int KS, int XL, int KIND, bool CKPT, int OUTK, typename V>
 __device__ __forceinline__ void fwd_pass(const FwdParams& p, LaneState<R, T, V>& L,
                                          const PassGeom& G, const V* prev_row, V* s_ref,
                                          V* s_hand, V* s_slot) {
+  using S = FwdShape<R, T, W, KS, XL>;
   const int tid = team_tid<W>();
-  V rvA[T], injA[T], rvB[T], injB[T];
-  step_inputs<R, T, W, KS, XL>(rvA, injA, 0, G, s_ref, s_hand, s_slot);
+  V rv[2][T], top[2][T];
+  GroupPtrs<V> P = group_ptrs<R, T, W, KS, XL, V>(0, G, s_ref, s_hand);
+  tile_load<T, S::REFP>(rv[0], P.ref);
+  if constexpr (!XL) tile_load<T, S::HANDP>(top[0], P.top);
   for (int it = 0; it < G.nint; ++it) {
     Stager<R, T, W, KS, XL, V> st;
     st.load(p.reference, p.ref_len, prev_row, G.ntiles * T, (it + 2) * KS, tid);
@@ -526,14 +652,14 @@ __device__ __forceinline__ void fwd_pass(const FwdParams& p, LaneState<R, T, V>&
     if (!G.idle) {
       if constexpr (CKPT) {
         if (G.ck_each_step)
-          fwd_steps<R, T, W, KS, XL, KIND, kCkEachStep, OUTK, V>(p, L, G, it, rvA, injA, rvB,
-                                                                 injB, s_ref, s_hand, s_slot);
+          fwd_steps<R, T, W, KS, XL, KIND, kCkEachStep, OUTK, V>(p, L, G, it, rv, top, P, s_ref,
+                                                                 s_hand, s_slot);
         else
-          fwd_steps<R, T, W, KS, XL, KIND, kCkSelect, OUTK, V>(p, L, G, it, rvA, injA, rvB, injB,
-                                                               s_ref, s_hand, s_slot);
+          fwd_steps<R, T, W, KS, XL, KIND, kCkSelect, OUTK, V>(p, L, G, it, rv, top, P, s_ref,
+                                                               s_hand, s_slot);
       } else {
-        fwd_steps<R, T, W, KS, XL, KIND, kCkNone, OUTK, V>(p, L, G, it, rvA, injA, rvB, injB,
-                                                           s_ref, s_hand, s_slot);
+        fwd_steps<R, T, W, KS, XL, KIND, kCkNone, OUTK, V>(p, L, G, it, rv, top, P, s_ref,
+                                                           s_hand, s_slot);
       }
     }
     // The stager's commit waits for its loads with a vmcnt wait, which on
@@ -544,11 +670,10 @@ __device__ __forceinline__ void fwd_pass(const FwdParams& p, LaneState<R, T, V>&
     if constexpr (CKPT) {
       if (!G.ck_each_step) ckpt_flush<R, T, KS>(p, L, G, it);
       if (G.rowck != nullptr)
-        rowck_copy<T, KS, FwdShape<R, T, W, KS, XL>::SH>(p, G, reinterpret_cast<float*>(s_hand),
-                                                          it);
+        rowck_copy<T, KS, S::SH, S::HANDP>(p, G, reinterpret_cast<float*>(s_hand), it);
       if constexpr (R * kWave > kRowCkpt) {
         if (G.rowck_mid != nullptr)
-          rowck_mid_copy<R, T, KS, FwdShape<R, T, W, KS, XL>::SH>(p, G, it);
+          rowck_mid_copy<R, T, KS, S::SH>(p, G, it);
       }
     }
     if constexpr (OUTK >= 0) {
@@ -616,6 +741,10 @@ __device__ __forceinline__ void fwd_one_pass(const FwdParams& p, int b, PassGeom
     }
     L.dl[k] = Val<V>::inf();
   }
+  // (wait for the query values now: a wait inside the step loop would also
+  // cover the reference loads that every barrier interval issues first)
+#pragma unroll
+  for (int k = 0; k < RR; ++k) in_register(L.qv[k]);
 #pragma unroll
   for (int t = 0; t < T; ++t) L.bot[t] = Val<V>::inf();
   L.corner = Val<V>::inf();
@@ -645,9 +774,9 @@ __device__ __forceinline__ void fwd_one_pass(const FwdParams& p, int b, PassGeom
   // see +inf), a zeroed reference ring (so that those lanes compute on
   // finite values, never on whatever the LDS held), then the first two
   // intervals of reference and top boundary.
-  for (int e = tid; e < W * S::SH * T; e += S::THREADS) s_hand[e] = Val<V>::inf();
+  for (int e = tid; e < W * S::HAND; e += S::THREADS) s_hand[e] = Val<V>::inf();
   for (int e = tid; e < S::SLOTS; e += S::THREADS) s_slot[e] = Val<V>::inf();
-  for (int e = tid; e < S::SR * T; e += S::THREADS) s_ref[e] = Val<V>::zero();
+  for (int e = tid; e < S::REFRING; e += S::THREADS) s_ref[e] = Val<V>::zero();
   team_sync<W>();
   {
     Stager<RR, T, W, KS, XL, V> st0, st1;
@@ -701,8 +830,8 @@ __device__ __forceinline__ void fwd_query(const FwdParams& p, int b, int64_t qof
   static_assert(RT == R || RT == R / 2 || RT == R / 4, "tail passes hold R/2 or R/4 rows");
   using S0 = FwdShape<R, T, W, KS, XL>;
   V* s_ref = reinterpret_cast<V*>(s_mem);
-  V* s_hand = s_ref + S0::SR * T;
-  V* s_slot = s_hand + W * S0::SH * T;
+  V* s_hand = s_ref + S0::REFRING;
+  V* s_slot = s_hand + W * S0::HAND;
   using S = FwdShape<R, T, W, KS, XL>;
   const int tid = team_tid<W>();
   PassGeom G;
