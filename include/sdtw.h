@@ -106,7 +106,10 @@ enum {
  * lane, W wavefronts per query: sdtw_variant_info); the plain launch gives a
  * slot to each query longer than one pass, the persistent launch one to each
  * of its teams when some query is.  A batch whose queries all fit in
- * one pass needs no row buffer.  cost and end_pos are reduced on chip.
+ * one pass needs no row buffer.  A column-owning variant (rows per lane 1 in
+ * sdtw_variant_info) has no passes and no row buffer; with a reference of
+ * more than 1,024 columns it holds 8 bytes per query row and 32 per query
+ * instead.  cost and end_pos are reduced on chip.
  */
 SDTW_API size_t sdtw_forward_workspace_bytes(const int32_t *h_query_lens, int32_t batch,
                                     int64_t ref_len, int32_t flags, int32_t variant);
@@ -189,8 +192,10 @@ SDTW_API int sdtw_forward(const float *queries, const int32_t *h_query_lens,
  * frees nothing.  Each GPU the library runs on holds its own array until the
  * process ends.
  *
- *   - A batch whose sdtw_forward_workspace_bytes(..., flags, variant)
- *     exceeds SDTW_NOALLOC_SCRATCH_BYTES is rejected with SDTW_ERR_WORKSPACE
+ *   - With variant -1 the library chooses among the variants whose workspace
+ *     fits the array.  A batch whose sdtw_forward_workspace_bytes(..., flags,
+ *     variant) exceeds SDTW_NOALLOC_SCRATCH_BYTES for the given variant, or
+ *     for every variant, is rejected with SDTW_ERR_WORKSPACE
  *     before anything is enqueued.  That covers any batch of up to about a
  *     million queries that fit in one row pass of the tile, plus
  *     SDTW_NOALLOC_SCRATCH_BYTES / (4 * ref_len) row-buffer slots for
@@ -411,7 +416,10 @@ SDTW_API int32_t sdtw_variant_count(void);
 /*
  * Describe variant v: query rows held per lane, reference columns per step,
  * wavefronts per query, steps between workgroup barriers, and how a lane's
- * bottom row reaches the next lane (1: through LDS, 0: DPP lane shift).  Any
+ * bottom row reaches the next lane (1: through LDS, 0: DPP lane shift).  Rows
+ * per lane 1 marks the column-owning form: lanes own tile_cols * waves
+ * adjacent reference columns and walk down the query, one wavefront per
+ * segment of 64 lanes; its plain and persistent launches are the same.  Any
  * output pointer may be NULL.  Returns SDTW_OK or SDTW_ERR_UNSUPPORTED.
  */
 SDTW_API int sdtw_variant_info(int32_t v, int32_t *rows_per_lane, int32_t *tile_cols,

@@ -17,6 +17,7 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libsdtw.so")
 API_SOURCE = os.path.join(HERE, "sdtw_api.hip")
 VARIANT_SOURCE = os.path.join(HERE, "sdtw_variant_tu.hip")
+COLS_SOURCE = os.path.join(HERE, "sdtw_cols_tu.hip")       # entries with R = 1
 VARIANT_LIST = os.path.join(HERE, "sdtw_variants.inc")
 OBJ_DIR = os.path.join(os.path.dirname(os.path.dirname(HERE)), "_build", "sdtw")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -57,7 +58,8 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     units = [(API_SOURCE, os.path.join(OBJ_DIR, "sdtw_api.o"), [])]
     for i, r, t, w, ks, xl in variants():
-        units.append((VARIANT_SOURCE, os.path.join(OBJ_DIR, f"sdtw_variant_{i}.o"),
+        source = COLS_SOURCE if r == 1 else VARIANT_SOURCE
+        units.append((source, os.path.join(OBJ_DIR, f"sdtw_variant_{i}.o"),
                       [f"-DSDTW_VARIANT_INDEX={i}", f"-DSDTW_R={r}", f"-DSDTW_T={t}",
                        f"-DSDTW_W={w}", f"-DSDTW_KS={ks}", f"-DSDTW_XL={xl}"]))
     jobs = jobs or min(len(units), max(1, min(16, os.cpu_count() or 1)))

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -12,6 +13,7 @@
 #include "sdtw.h"
 #include "sdtw_argmin.hpp"
 #include "sdtw_bwd.hpp"
+#include "sdtw_cols.hpp"
 #include "sdtw_fwd.hpp"
 #include "sdtw_quant.hpp"
 #include "sdtw_setup.hpp"
@@ -79,12 +81,15 @@ constexpr int32_t kInKernelOffsetBatch = 16384;
 // Forward workspace: offset and slot tables (used above kInKernelOffsetBatch
 // queries), the persistent form's work counter and processing order, and the
 // row buffer that carries the last row of a row pass to the next pass.
+// The column-owning form needs no row buffer but the words that carry the
+// segments' right-most columns.
 struct FwdLayout {
-  size_t offsets, ranks, queue, order, rowbuf, total;
+  size_t offsets, ranks, queue, order, rowbuf, edges, total;
   int64_t slots;
 };
 
-FwdLayout fwd_layout(int32_t batch, int64_t ref_len, int32_t flags, int64_t slots) {
+FwdLayout fwd_layout(int32_t batch, int64_t ref_len, int32_t flags, int64_t slots,
+                     int64_t edge_words) {
   FwdLayout L{};
   size_t at = 0;
   L.offsets = at;
@@ -98,8 +103,18 @@ FwdLayout fwd_layout(int32_t batch, int64_t ref_len, int32_t flags, int64_t slot
   L.rowbuf = at;
   L.slots = slots;
   at = align_up(at + sizeof(float) * (size_t)slots * (size_t)row_stride_floats(ref_len), kAlign);
+  L.edges = at;
+  at = align_up(at + sizeof(unsigned long long) * (size_t)edge_words, kAlign);
   L.total = at;
   return L;
+}
+
+// Edge words of a forward launch of variant v: none when the reference is a
+// single segment of the narrowest column-owning form (which may stand in for
+// a wider one when checkpointing).
+int64_t fwd_edge_words(const Variant& v, int64_t total_len, int32_t batch, int64_t ref_len) {
+  return v.cols && ref_len > sdtw::kWave * kCkptQuantum
+             ? sdtw::cols_edge_words(total_len, batch) : 0;
 }
 
 // uint8-code forward: the plain forward's workspace, then the codes of the
@@ -112,7 +127,8 @@ struct U8Layout {
 
 U8Layout u8_layout(int32_t batch, int64_t total_rows, int64_t ref_len) {
   U8Layout L{};
-  L.fwd = fwd_layout(batch, ref_len, 0, batch);   // one row-buffer slot per query
+  // one row-buffer slot per query, and room for the column-owning form
+  L.fwd = fwd_layout(batch, ref_len, 0, batch, sdtw::cols_edge_words(total_rows, batch));
   size_t at = L.fwd.total;
   L.qcodes = at;
   at = align_up(at + (size_t)total_rows, kAlign);
@@ -159,6 +175,7 @@ int64_t persistent_grid_for(const Variant& v, int32_t batch, int cus, int32_t fl
 // second pass.  Queries that fit in one pass never touch the row buffer.
 int64_t fwd_slots(const Variant& v, const int32_t* h_lens, int32_t batch, int32_t flags,
                   int cus) {
+  if (v.cols) return 0;
   const int64_t rows = 64LL * v.R * v.W;
   int64_t multi = 0;
   for (int32_t b = 0; b < batch; ++b) multi += h_lens[b] > rows ? 1 : 0;
@@ -179,37 +196,97 @@ int64_t n_ckpt_of(int64_t ref_len, int32_t every) {
   return (ref_len + every - 1) / every - 1;
 }
 
-// Estimated relative time of a variant on this batch (used when the caller
-// lets the library choose): padded cells x VALU instructions per cell over
-// the issue rate the launch can sustain.  gfx950 dual-issues VALU from two
-// ready wavefronts of a SIMD, so the rate grows with resident wavefronts per
-// SIMD (factors measured on 512 x 2,000 vs 100,000 and 256 x 1,000 vs 50,000).
-double variant_cost(const Variant& v, const int32_t* h_lens, int32_t batch, int64_t ref_len,
-                    int cus) {
-  const int64_t rows = 64LL * v.R * v.W;
-  const int64_t ntiles = (ref_len + v.T - 1) / v.T;
-  // pipeline fill: each lane lags its neighbour by one step (both exchange
-  // forms), each wavefront the previous one by KS steps more
-  const int64_t skew = (64LL * v.W - 1) + (v.W - 1) * v.KS;
-  double cells = 0;
+// What the choice of a variant needs to know of a batch: how many queries
+// need u blocks of 64 rows (pass and wavefront counts depend on nothing else).
+struct BatchShape {
+  std::vector<int32_t> blocks;       // [u]: queries of u blocks
+  int32_t batch, nmax;
+  int64_t total;
+};
+
+BatchShape batch_shape(const int32_t* h_lens, int32_t batch) {
+  BatchShape s{};
+  s.batch = batch;
+  for (int32_t b = 0; b < batch; ++b) s.nmax = std::max(s.nmax, h_lens[b]);
+  s.blocks.assign((size_t)(s.nmax / 64) + 2, 0);
   for (int32_t b = 0; b < batch; ++b) {
-    const int64_t passes = (h_lens[b] + rows - 1) / rows;
-    cells += (double)passes * rows * (double)(ntiles + skew) * v.T;
+    s.total += h_lens[b];
+    ++s.blocks[((size_t)h_lens[b] + 63) / 64];
   }
-  // per-cell VALU work: 4 cell ops and about 8 per-step instructions; the
-  // DPP form adds one move per row-block column, and its DPP moves cost
-  // dual issue (about 10 % measured at R = 8)
-  const double per_cell =
-      (4.0 + 8.0 / (v.R * v.T) + (v.XL ? 0.0 : 1.0 / v.R)) * (v.XL ? 1.0 : 1.1);
-  // wavefronts per SIMD: the batch's, capped by the workgroups one CU holds
-  // (160 KiB of LDS, 32 wavefronts)
+  return s;
+}
+
+// Estimated time (us) of a variant on a batch, from step times measured on
+// gfx950; it decides what the library runs when the caller leaves the choice
+// to it.
+//
+// Column-owning form, C = 16 (32) columns per lane: a step takes 0.165
+// (0.275) us alone on its SIMD and 0.09 (0.20) us of a SIMD's time when it is
+// shared; a segment starts 18 (29) us behind the one before it.  So a few
+// queries are bound by the chain of segments and many by the SIMDs; fill and
+// drain cost a walk down the longest query.  Measured / estimated, us: 1 x
+// 2,000 vs 100,000 2,062 / 2,086, 512 x 1,000 vs 20,000 1,223 / 1,090, 512 x
+// 250 vs 20,000 531 / 450.  Checkpoints cost it a quarter.
+//
+// Row-owning tiles: a step takes 0.05 + 0.010 T + 0.0069 R T us with DPP
+// exchange and 0.09 + 0.004 T + 0.0080 R T us through LDS with two wavefronts
+// per SIMD, about 8 % less with one, proportionally more with more; steps per
+// pass are the tiles of the reference and the fill (each lane lags its
+// neighbour by one step, each wavefront the one before by KS more).  512 x
+// 2,000 vs 100,000, (8,8,4,16) DPP: 7,198 / 7,272; 512 x 1,000 vs 20,000,
+// (4,8,4,8): 1,013 / 970.  A barrier interval with checkpoints costs 0.25 +
+// 0.1 R us more.
+double variant_cost(const Variant& v, const BatchShape& s, int64_t ref_len, int32_t flags,
+                    int cus) {
+  const double simds = 4.0 * cus;
+  const bool ck = (flags & SDTW_F_CHECKPOINT) != 0;
+  if (v.cols) {
+    const bool wide = v.cols > kCkptQuantum;
+    const double step = wide ? 0.275 : 0.165, shared = wide ? 0.20 : 0.09;
+    const double hop = wide ? 29.0 : 18.0;
+    const double nseg = (double)((ref_len + 64 * v.cols - 1) / (64 * v.cols));
+    const double drain = (s.nmax + 63.0) * step;
+    const double chain = (nseg - 1) * hop + drain;
+    const double work =
+        nseg * ((double)s.total + 63.0 * s.batch) / simds * shared + 0.5 * drain;
+    return std::pow(std::pow(chain, 2.5) + std::pow(work, 2.5), 1.0 / 2.5) * (ck ? 1.25 : 1.0) +
+           (nseg > 1 ? 8.0 : 0.0);
+  }
+  const int64_t per_pass = (int64_t)v.R * v.W;           // blocks of 64 rows
+  const double ntiles = (double)((ref_len + v.T - 1) / v.T);
+  const double steps = ntiles + 64.0 * v.W + (double)(v.W - 1) * v.KS;
+  const bool persistent = (flags & SDTW_F_PERSISTENT) != 0;
+  double passes = 0, waves = 0;                          // of all queries
+  for (size_t u = 1; u < s.blocks.size(); ++u) {
+    if (s.blocks[u] == 0) continue;
+    const int64_t full = ((int64_t)u - 1) / per_pass;
+    const int64_t left = (int64_t)u - full * per_pass;   // blocks of the last pass
+    double last = 1.0;
+    if (persistent && !ck && v.R >= 4) {                 // tail passes of fewer rows per lane
+      const double quarter = std::ceil(4.0 * left / per_pass) / 4;
+      last = 0.1 + 0.9 * (v.R >= 8 ? quarter : std::max(0.5, std::ceil(2 * quarter) / 2));
+    }
+    passes += s.blocks[u] * (full + last);
+    waves += s.blocks[u] * (double)(full * v.W + (left + v.R - 1) / v.R);
+  }
+  const double maxpass = (double)(((s.nmax + 63) / 64 + per_pass - 1) / per_pass);
+  // workgroups side by side on a CU (160 KiB of LDS, at most 16 wavefronts)
+  // and the wavefronts they keep busy per SIMD
   constexpr int kLdsPerCu = 160 * 1024;
-  const int wg_per_cu = std::max(1, std::min(kLdsPerCu / std::max(1, v.lds_bytes), 32 / v.W));
-  const double wps = std::min((double)batch * v.W / (4.0 * cus), wg_per_cu * v.W / 4.0);
-  static const double kIssue[] = {0.0, 0.55, 0.75, 0.85, 1.0};   // by min(4, ceil(wps))
-  const int slot = wps <= 0 ? 1 : (wps >= 4 ? 4 : (int)(wps + 0.999));
-  const double rate = kIssue[slot] * std::min(1.0, wps / slot);
-  return cells * per_cell / rate;
+  int fit = std::max(1, std::min(kLdsPerCu / std::max(1, v.lds_bytes), 16 / v.W));
+  if (persistent) {
+    const int wps = (flags & SDTW_F_WAVES_MASK) >> SDTW_F_WAVES_SHIFT;
+    fit = std::max(1, 4 * (wps > 0 ? wps : 2) / v.W);
+  }
+  const double side = std::min<double>(fit, std::ceil((double)s.batch / cus));
+  const double busy = std::max(1.0, side * waves / std::max(1.0, passes) / 4.0);
+  const double two = v.XL ? 0.09 + 0.004 * v.T + 0.0080 * v.R * v.T
+                          : 0.05 + 0.010 * v.T + 0.0069 * v.R * v.T;
+  const double step = busy <= 2.0 ? two * (0.92 + 0.08 * (busy - 1.0)) : two * busy / 2.0;
+  const double rounds = passes / (cus * side);
+  double t = std::max(maxpass, rounds > 1.0 ? 1.05 * rounds : 1.0) * steps * step;
+  if (ck) t += std::max(maxpass, rounds) * steps / v.KS * (0.25 + 0.1 * v.R);
+  return t + (persistent ? 8.0 : 0.0);
 }
 
 // Compute units of the current device (read once per device; a CPX or other
@@ -244,18 +321,36 @@ void* scratch_address() {
   return addr[dev];
 }
 
-int pick_variant(const int32_t* h_lens, int32_t batch, int64_t ref_len, int32_t flags, int cus) {
-  (void)flags;
-  int best = 0;
-  double best_cost = 0;
+// Row-buffer slots and edge words of a forward launch: its workspace.
+FwdLayout fwd_layout_of(const Variant& v, const int32_t* h_lens, int32_t batch, int64_t total,
+                        int64_t ref_len, int32_t flags, int cus) {
+  return fwd_layout(batch, ref_len, flags, fwd_slots(v, h_lens, batch, flags, cus),
+                    fwd_edge_words(v, total, batch, ref_len));
+}
+
+// The variant with the smallest estimate, among those whose workspace is at
+// most max_bytes if any is (callers that cannot give more).
+int pick_variant(const int32_t* h_lens, int32_t batch, int64_t ref_len, int32_t flags, int cus,
+                 size_t max_bytes = SIZE_MAX) {
+  const BatchShape s = batch_shape(h_lens, batch);
+  int best = -1, best_any = 0;
+  double best_cost = 0, best_any_cost = 0;
   for (int i = 0; i < variant_count(); ++i) {
-    const double c = variant_cost(variant(i), h_lens, batch, ref_len, cus);
-    if (i == 0 || c < best_cost) {
+    const Variant& v = variant(i);
+    const double c = variant_cost(v, s, ref_len, flags, cus);
+    if (i == 0 || c < best_any_cost) {
+      best_any = i;
+      best_any_cost = c;
+    }
+    if (max_bytes != SIZE_MAX &&
+        fwd_layout_of(v, h_lens, batch, s.total, ref_len, flags, cus).total > max_bytes)
+      continue;
+    if (best < 0 || c < best_cost) {
       best = i;
       best_cost = c;
     }
   }
-  return best;
+  return best >= 0 ? best : best_any;
 }
 
 // Backward: direction codes of `slots` blocks per query are held per round,
@@ -349,6 +444,75 @@ ZLayout znorm_layout(const int32_t* h_lens, int32_t batch) {
 int launch(const void* fn, dim3 grid, dim3 block, void** args, hipStream_t stream) {
   hipError_t e = hipLaunchKernel(fn, grid, block, args, 0, stream);
   return e == hipSuccess ? SDTW_OK : SDTW_ERR_HIP;
+}
+
+// The column-owning variant that runs a call of variant v: with checkpoints,
+// whose columns must be some lane's last, the narrowest one when ckpt_every
+// is not a multiple of v's columns per lane.
+const Variant& cols_variant(const Variant& v, int ck, int32_t ckpt_every) {
+  if (!ck || ckpt_every % v.cols == 0) return v;
+  for (int i = 0; i < variant_count(); ++i)
+    if (variant(i).cols == kCkptQuantum) return variant(i);
+  return v;
+}
+
+// Launch of the column-owning form: offsets, item counter and edge words
+// first, then as many wavefronts as can have work at once.  A query's next
+// segment starts 64 steps (and the handover of eight rows) behind the one
+// before it, so of a query of n rows about (n + 63) / 72 segments are under
+// way at a time; more workgroups would only wait.  A reference of a single segment
+// needs neither counter nor edges: one launch.
+int cols_launch(const Variant& v, const void* fn, const FwdParams& f, const int32_t* unit_lens,
+                int32_t units, int64_t total, const FwdLayout& L, char* ws, int32_t flags,
+                int cus, hipStream_t stream) {
+  sdtw::ColsParams p{};
+  p.queries = f.queries;
+  p.lens = f.lens;
+  p.offsets = nullptr;
+  p.reference = f.reference;
+  p.cost = f.cost;
+  p.end_pos = f.end_pos;
+  p.ckpt = f.ckpt;
+  p.rowck = f.rowck;
+  p.edges = reinterpret_cast<unsigned long long*>(ws + L.edges);
+  p.queue = nullptr;
+  p.batch = f.batch;
+  p.units = units;
+  p.ref_len = f.ref_len;
+  p.nseg = (f.ref_len + sdtw::kWave * v.cols - 1) / (sdtw::kWave * v.cols);
+  p.ckpt_every = f.ckpt_every;
+  p.n_ckpt = f.n_ckpt;
+  p.prune_tau = f.prune_tau;
+  constexpr int kWaves = sdtw::kColsWaves;
+  int64_t groups = ((int64_t)units + kWaves - 1) / kWaves;    // workgroups
+  if (p.nseg > 1 || f.batch > kInKernelOffsetBatch) {
+    int64_t* offs = reinterpret_cast<int64_t*>(ws + L.offsets);
+    unsigned long long* queue = reinterpret_cast<unsigned long long*>(ws + L.queue);
+    unsigned long long* edges = p.edges;
+    const int32_t* lens = f.lens;
+    int32_t batch = f.batch;
+    int64_t words = p.nseg > 1 ? sdtw::cols_edge_words(total, f.batch) : 0;
+    const int64_t fill = (words + sdtw::kScanThreads - 1) / sdtw::kScanThreads;
+    void* args[] = {(void*)&lens, (void*)&batch, (void*)&offs, (void*)&queue, (void*)&edges,
+                    (void*)&words};
+    const int rc = launch(reinterpret_cast<const void*>(&sdtw::sdtw_cols_init_kernel),
+                          dim3((unsigned)(1 + std::min<int64_t>(fill, 1024))),
+                          dim3(sdtw::kScanThreads), args, stream);
+    if (rc != SDTW_OK) return rc;
+    p.offsets = offs;
+    if (p.nseg > 1) p.queue = queue;
+  }
+  if (p.queue != nullptr) {
+    const int wps = (flags & SDTW_F_WAVES_MASK) >> SDTW_F_WAVES_SHIFT;
+    const int64_t cap = (int64_t)cus * (wps > 0 ? wps : v.cols >= 32 ? 2 : 4);
+    const int64_t items = (int64_t)units * ((p.nseg + kWaves - 1) / kWaves);
+    int64_t ready = 0;
+    for (int32_t u = 0; u < units && ready < cap; ++u)
+      ready += (unit_lens[u] + 63 + 72 * (kWaves - 1)) / (72 * kWaves) + 2;
+    groups = std::min({items, cap, ready});
+  }
+  void* args[] = {(void*)&p};
+  return launch(fn, dim3((unsigned)groups), dim3(sdtw::kColsThreads), args, stream);
 }
 
 // Parameters shared by the walk-back entry points (sdtw_backward, sdtw_align).
@@ -502,14 +666,14 @@ int32_t sdtw_default_variant(const int32_t* h_query_lens, int32_t batch, int64_t
 
 size_t sdtw_forward_workspace_bytes(const int32_t* h_query_lens, int32_t batch, int64_t ref_len,
                                     int32_t flags, int32_t variant_id) {
-  if (!lens_ok(h_query_lens, batch, nullptr, nullptr) || !ref_ok(ref_len)) return 0;
+  int64_t total = 0;
+  if (!lens_ok(h_query_lens, batch, &total, nullptr) || !ref_ok(ref_len)) return 0;
   if (!fwd_flags_ok(flags)) return 0;
   if (variant_id < -1 || variant_id >= variant_count()) return 0;
   const int cus = device_cus();
   const int vid = variant_id >= 0 ? variant_id
                                   : pick_variant(h_query_lens, batch, ref_len, flags, cus);
-  const int64_t slots = fwd_slots(variant(vid), h_query_lens, batch, flags, cus);
-  return fwd_layout(batch, ref_len, flags, slots).total;
+  return fwd_layout_of(variant(vid), h_query_lens, batch, total, ref_len, flags, cus).total;
 }
 
 size_t sdtw_checkpoint_floats(const int32_t* h_query_lens, int32_t batch, int64_t ref_len,
@@ -552,12 +716,15 @@ int forward_impl(const float* queries, const int32_t* h_query_lens, const int32_
   const bool persistent = (flags & SDTW_F_PERSISTENT) != 0;
   const int cus = device_cus();
   const int vid = variant_id >= 0 ? variant_id
-                                  : pick_variant(h_query_lens, batch, ref_len, flags, cus);
+                                  : pick_variant(h_query_lens, batch, ref_len, flags, cus,
+                                                 use_scratch ? SDTW_NOALLOC_SCRATCH_BYTES
+                                                             : SIZE_MAX);
   const Variant& v = variant(vid);
   // the uint8-code kernel indexes the row buffer by query
-  const int64_t slots = cost_kind == kU8Codes ? batch
+  const int64_t slots = cost_kind == kU8Codes && !v.cols ? batch
                                               : fwd_slots(v, h_query_lens, batch, flags, cus);
-  const FwdLayout L = fwd_layout(batch, ref_len, flags, slots);
+  const FwdLayout L =
+      fwd_layout(batch, ref_len, flags, slots, fwd_edge_words(v, total, batch, ref_len));
   if (use_scratch) {
     // the library's own array (256-byte aligned), checked against its size
     // before any HIP call
@@ -592,6 +759,13 @@ int forward_impl(const float* queries, const int32_t* h_query_lens, const int32_
   const int ck = p.ckpt != nullptr ? 1 : 0;
   const bool pruned = cost_kind == sdtw::kPruned;
 
+  if (v.cols) {
+    const Variant& c = cols_variant(v, ck, ckpt_every);
+    const void* fn = cost_kind == kU8Codes ? c.u8
+                     : pruned              ? c.pruned[0]
+                                           : c.plain[cost_kind][ck];
+    return cols_launch(c, fn, p, h_query_lens, batch, total, L, ws, flags, cus, stream);
+  }
   if (batch > kInKernelOffsetBatch) {
     // offset and row-buffer slot tables; smaller batches let each workgroup
     // sum the lengths before its query instead
@@ -733,9 +907,11 @@ int sdtw_forward_u8(const float* queries, const int32_t* h_query_lens, const int
 
 size_t sdtw_forward_f16_workspace_bytes(const int32_t* h_query_lens, int32_t batch,
                                         int64_t ref_len) {
-  if (!lens_ok(h_query_lens, batch, nullptr, nullptr) || !ref_ok(ref_len)) return 0;
+  int64_t total = 0;
+  if (!lens_ok(h_query_lens, batch, &total, nullptr) || !ref_ok(ref_len)) return 0;
   if (f16_pair_lens(h_query_lens, batch).empty()) return 0;
-  return fwd_layout(batch, ref_len, 0, (batch + 1) / 2).total;
+  return fwd_layout(batch, ref_len, 0, (batch + 1) / 2, sdtw::cols_edge_words(total, batch))
+      .total;
 }
 
 int sdtw_forward_f16(const float* queries, const int32_t* h_query_lens,
@@ -745,7 +921,8 @@ int sdtw_forward_f16(const float* queries, const int32_t* h_query_lens,
                      void* stream_ptr) {
   if (!queries || !query_lens || !reference || !cost || !end_pos || !workspace)
     return SDTW_ERR_INVALID_ARG;
-  if (!lens_ok(h_query_lens, batch, nullptr, nullptr) || !ref_ok(ref_len))
+  int64_t total = 0;
+  if (!lens_ok(h_query_lens, batch, &total, nullptr) || !ref_ok(ref_len))
     return SDTW_ERR_INVALID_ARG;
   if (cost_kind != SDTW_COST_SQUARED && cost_kind != SDTW_COST_ABSOLUTE)
     return SDTW_ERR_INVALID_ARG;
@@ -754,10 +931,12 @@ int sdtw_forward_f16(const float* queries, const int32_t* h_query_lens,
   if (pl.empty()) return SDTW_ERR_UNSUPPORTED;
   if (variant_id < -1 || variant_id >= variant_count()) return SDTW_ERR_UNSUPPORTED;
   const int32_t pairs = (batch + 1) / 2;
-  const FwdLayout L = fwd_layout(batch, ref_len, 0, pairs);
+  const FwdLayout L =
+      fwd_layout(batch, ref_len, 0, pairs, sdtw::cols_edge_words(total, batch));
   if (workspace_bytes < L.total) return SDTW_ERR_WORKSPACE;
+  const int cus = device_cus();
   const int vid = variant_id >= 0 ? variant_id
-                                  : pick_variant(pl.data(), pairs, ref_len, 0, device_cus());
+                                  : pick_variant(pl.data(), pairs, ref_len, 0, cus);
   const Variant& v = variant(vid);
   hipStream_t stream = reinterpret_cast<hipStream_t>(stream_ptr);
   char* ws = static_cast<char*>(workspace);
@@ -773,6 +952,8 @@ int sdtw_forward_f16(const float* queries, const int32_t* h_query_lens,
   p.row_stride = row_stride_floats(ref_len);
   p.batch = batch;
   p.ref_len = (int32_t)ref_len;
+  if (v.cols)
+    return cols_launch(v, v.half[cost_kind], p, pl.data(), pairs, total, L, ws, 0, cus, stream);
   if (batch > kInKernelOffsetBatch) {
     int64_t* offs = reinterpret_cast<int64_t*>(ws + L.offsets);
     int32_t rows = 0;

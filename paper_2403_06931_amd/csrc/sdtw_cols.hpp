@@ -1,0 +1,457 @@
+// sdtw_cols.hpp -- forward sDTW DP fill with lanes owning reference columns
+// (the mapping of the paper's Section 5.2 kernel, there one wavefront over
+// the whole reference).
+//
+//   * the reference is cut into segments of 64 C columns; one wavefront
+//     computes one segment of one query: lane l owns C adjacent columns,
+//     holds their reference values and DP values in registers and walks down
+//     the query rows, one row per step, one step behind lane l-1;
+//   * per step only two values move between lanes, the right-most DP value
+//     and the row's query value (DPP wave_shr:1), for C cells; the row-owning
+//     kernel moves a whole tile row and re-reads the reference tile from LDS
+//     for each R x T block, which is what bounds it when few rows per lane
+//     are needed to fill the chip;
+//   * segment s of a query needs the right-most column of segment s-1, which
+//     the wavefront of segment s-1 hands over 8 rows at a time.  The four
+//     wavefronts of a workgroup take four segments in a row and hand over
+//     through an LDS ring; the last segment of a workgroup is published in
+//     global memory, each value beside the number of its segment in one
+//     8-byte word, and the wavefront of the next segment reads it 8 rows ahead
+//     of its lane 0.  The word of a row is overwritten in place by the
+//     workgroup that has read it, so a query needs one word per row, and a
+//     word is valid as soon as it carries the expected segment: no fence, no
+//     flag and no reset.  (A handover through global memory takes about 6 us
+//     between two XCDs, one through LDS well under one; a segment starts 64
+//     steps, 12 to 17 us, behind the one before it.)
+//
+// Workgroups take (four segments, query) items from a counter, segments in
+// increasing order.  Why every wait ends, whatever the order in which
+// workgroups start and however many of them are resident: a wavefront waits
+// for the wavefront before it in its workgroup (the same item), for room in
+// its ring, i.e. for the wavefront behind it to read rows it already has
+// (which that one does after finishing earlier items), and, the first one,
+// for the item of the same query and the segments before, which was handed
+// out earlier, hence to a workgroup that is running; the item that was handed
+// out first waits for no other.  Wavefront 0 takes the items and runs at most
+// kColsTickets of them ahead of the others.
+#pragma once
+
+#include "sdtw_argmin.hpp"
+#include "sdtw_common.hpp"
+#include "sdtw_value.hpp"
+
+namespace sdtw {
+
+constexpr int kColsThreads = 4 * kWave;         // four independent wavefronts
+constexpr int kColsRows = 8;                    // rows per step group and per published chunk
+
+struct ColsParams {
+  const float* queries;         // packed
+  const int32_t* lens;          // [batch]
+  const int64_t* offsets;       // [batch + 1], or nullptr: summed by the wavefront
+  const float* reference;       // [ref_len]
+  float* cost;                  // [batch]
+  int64_t* end_pos;             // [batch]
+  float* ckpt;                  // checkpoint columns, or nullptr
+  float* rowck;                 // row checkpoints (with ckpt)
+  unsigned long long* edges;    // per query: its rows' words, then its running minimum
+  unsigned long long* queue;    // item counter, or nullptr: one item per wavefront
+  int32_t batch;
+  int32_t units;                // queries, or pairs of queries (binary16)
+  int32_t ref_len;
+  int32_t nseg;                 // segments, ceil(ref_len / (64 C))
+  int32_t ckpt_every;
+  int32_t n_ckpt;
+  float prune_tau;
+};
+
+// Words of the edge buffer of a batch: one per row and up to four more per
+// query (value and index of the running minimum, of two queries in binary16).
+constexpr int kColsExtra = 4;
+__host__ __device__ constexpr int64_t cols_edge_words(int64_t total_len, int64_t batch) {
+  return total_len + kColsExtra * batch;
+}
+
+__device__ __forceinline__ unsigned long long edge_word(uint32_t value, int seg) {
+  return ((unsigned long long)(uint32_t)seg << 32) | value;
+}
+
+__device__ __forceinline__ void edge_put(unsigned long long* at, uint32_t value, int seg) {
+  __hip_atomic_store(at, edge_word(value, seg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ unsigned long long edge_get(const unsigned long long* at) {
+  return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// LDS of one wavefront: the rows' left edge and query value for lane 0 (two
+// groups in turn), every lane's right-most value over one group, and the
+// right-most column handed to the next wavefront: a ring of rows and, counted
+// over all items, the rows put into it and the rows read from it.
+constexpr int kColsWaves = kColsThreads / kWave;
+constexpr int kColsRing = 128;
+constexpr int kColsTickets = 4;
+
+template <typename V>
+struct ColsLds {
+  V in[2][kColsRows][2];
+  V out[kColsRows][kWave];
+  V ring[kColsRing];
+  uint32_t put, got;
+};
+
+// Items handed from wavefront 0 to the others: slot k % kColsTickets carries
+// k + 1 once its item is there; started[w] counts the items wavefront w has
+// read.
+struct ColsTickets {
+  int64_t item[kColsTickets];
+  uint32_t ready[kColsTickets];
+  uint32_t started[kColsWaves];
+};
+
+// Words that wavefronts of a workgroup exchange without a barrier.  The LDS
+// operations of one wavefront complete in order, so data written before such
+// a word is there for whoever has read the word.
+__device__ __forceinline__ uint32_t lds_get(const uint32_t* at) {
+  const uint32_t v = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  asm volatile("" ::: "memory");
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+__device__ __forceinline__ void lds_put(uint32_t* at, uint32_t v) {
+  asm volatile("" ::: "memory");
+  __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const int hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+  const int lo = __builtin_amdgcn_readfirstlane((int)(v & 0xffffffff));
+  return ((int64_t)hi << 32) | (uint32_t)lo;
+}
+
+// What a wavefront knows about its item, uniform except `lane`.
+struct ColsItem {
+  int lane, b, n, seg, nseg, cs;
+  int64_t qoff;
+  unsigned long long* edge;     // the query's words
+  bool from_lds, to_lds;        // the neighbouring segments are this workgroup's
+  uint32_t in_base, out_base;   // rows of earlier items in the two rings
+  int ck_stride, ck_first;      // checkpoint columns: every ck_stride-th lane from ck_first on
+  int ck_k;                     // checkpoint (1..n_ckpt) of lane ck_first
+};
+
+// The next group's left edge and query values, row g0 + lane for the first
+// kColsRows lanes: loaded one group ahead, then checked (and read again until
+// the segment before has published them) and put into LDS.
+template <typename V>
+struct ColsStage {
+  using In = typename Val<V>::In;
+  unsigned long long word;
+  In q, q2;
+
+  __device__ __forceinline__ bool mine(const ColsItem& I, int g0) const {
+    return I.lane < kColsRows && g0 + I.lane < I.n;
+  }
+  __device__ __forceinline__ void load(const ColsItem& I, const In* __restrict__ qa,
+                                       const In* __restrict__ qb, int g0) {
+    word = 0;
+    q = In(0);
+    q2 = In(0);
+    if (mine(I, g0)) {
+      q = qa[g0 + I.lane];
+      if constexpr (Val<V>::N > 1) q2 = qb[g0 + I.lane];
+      if (I.seg > 0 && !I.from_lds) word = edge_get(I.edge + g0 + I.lane);
+    }
+  }
+  // `prev`: LDS of the wavefront before this one
+  __device__ __forceinline__ void commit(const ColsItem& I, ColsLds<V>& m, ColsLds<V>* prev,
+                                         int g0) {
+    V left = Val<V>::inf();
+    if (I.from_lds) {
+      const int last = g0 + kColsRows < I.n ? g0 + kColsRows : I.n;
+      if (last > g0) {
+        while ((int32_t)(lds_get(&prev->put) - (I.in_base + (uint32_t)last)) < 0)
+          __builtin_amdgcn_s_sleep(1);
+        left = prev->ring[(I.in_base + (uint32_t)(g0 + I.lane)) & (kColsRing - 1)];
+        lds_put(&prev->got, I.in_base + (uint32_t)last);
+      }
+    } else if (I.seg > 0) {
+      const bool need = mine(I, g0);
+      while (__ballot(need && (uint32_t)(word >> 32) != (uint32_t)(I.seg - 1)) != 0) {
+        __builtin_amdgcn_s_sleep(2);
+        if (need) word = edge_get(I.edge + g0 + I.lane);
+      }
+      left = __builtin_bit_cast(V, (uint32_t)word);
+    }
+    if (I.lane < kColsRows) {
+      V(&at)[2] = m.in[(g0 / kColsRows) & 1][I.lane];
+      at[0] = left;
+      at[1] = Val<V>::N > 1 ? Val<V>::query(q, q2) : Val<V>::query(q, In(0));
+    }
+  }
+};
+
+// State of a lane: its columns' reference values and the DP row above the
+// next one, the left neighbour's value on that row (the diagonal) and the
+// query value of the row before.
+template <int C, typename V>
+struct ColsLane {
+  V rv[C], d[C];
+  V shp, qv;
+  float tau;
+};
+
+// kColsRows steps from step g0 on: lane l is on row g - l + 1 at step g.
+// MASKED: some lanes are outside rows 1..n and keep their state.  ROWCK: a
+// lane's row may be a row checkpoint.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int C, int KIND, bool ROWCK, bool MASKED, typename V>
+__device__ __forceinline__ void cols_group(const ColsParams& p, const ColsItem& I,
+                                           ColsLane<C, V>& L, ColsLds<V>& m, int g0) {
+  V in[kColsRows][2];
+  const V(&src)[kColsRows][2] = m.in[(g0 / kColsRows) & 1];
+#pragma unroll
+  for (int s = 0; s < kColsRows; ++s) {
+    in[s][0] = src[s][0];
+    in[s][1] = src[s][1];
+  }
+#pragma unroll
+  for (int s = 0; s < kColsRows; ++s) {
+    V shc = in[s][0], q = in[s][1];
+    wave_shr1_pair(shc, L.d[C - 1], q, L.qv);
+    L.qv = q;
+    const int i = g0 + s - I.lane + 1;
+    if (!MASKED || (i >= 1 && i <= I.n)) {
+      V left = shc, diag = L.shp;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const V up = L.d[c];
+        L.d[c] = Val<V>::template cell<KIND>(L.qv, L.rv[c], up, left, diag, L.tau);
+        diag = up;
+        left = L.d[c];
+      }
+      if constexpr (ROWCK) {
+        if (i % kRowCkpt == 0 && i < I.n) {
+          const int j = I.cs + I.lane * C;
+          float* row = p.rowck + (I.qoff / kRowCkpt + i / kRowCkpt - 1) * (int64_t)p.ref_len + j;
+          if (j + C <= p.ref_len) {
+#pragma unroll
+            for (int c = 0; c < C; c += 4)
+              __builtin_nontemporal_store(f32x4u{L.d[c], L.d[c + 1], L.d[c + 2], L.d[c + 3]},
+                                          reinterpret_cast<f32x4u*>(row + c));
+          } else {
+            for (int c = 0; c < C; ++c)
+              if (j + c < p.ref_len) row[c] = L.d[c];
+          }
+        }
+      }
+    }
+    L.shp = shc;
+    m.out[s][I.lane] = L.d[C - 1];
+  }
+}
+
+// After a group: hand over the rows lane 63 finished in it (rows g0 - 63 + s,
+// 0-based) to the next segment, and store the checkpoint columns.
+template <int C, bool CKPT, typename V>
+__device__ __forceinline__ void cols_publish(const ColsParams& p, const ColsItem& I,
+                                             ColsLds<V>& m, int g0) {
+  const int s = I.lane & (kColsRows - 1);
+  const int row = g0 + s - (kWave - 1);
+  if (I.to_lds) {
+    const int last = g0 + kColsRows - (kWave - 1);             // rows done, at most n
+    const int done = last < I.n ? last : I.n;
+    if (done > 0) {
+      while ((int32_t)(I.out_base + (uint32_t)done - lds_get(&m.got)) > kColsRing)
+        __builtin_amdgcn_s_sleep(1);
+      if (I.lane < kColsRows && row >= 0 && row < I.n)
+        m.ring[(I.out_base + (uint32_t)row) & (kColsRing - 1)] = m.out[s][kWave - 1];
+      lds_put(&m.put, I.out_base + (uint32_t)done);
+    }
+  } else if (I.seg + 1 < I.nseg) {
+    const uint32_t v = __builtin_bit_cast(uint32_t, m.out[s][kWave - 1]);
+    if (I.lane < kColsRows && row >= 0 && row < I.n) edge_put(I.edge + row, v, I.seg);
+  }
+  if constexpr (CKPT) {
+    int k = I.ck_k + I.lane / kColsRows;
+    for (int l = I.ck_first + I.ck_stride * (I.lane / kColsRows);
+         __ballot(l < kWave) != 0; l += I.ck_stride * (kWave / kColsRows)) {
+      const int r = g0 + s - l;
+      if (l < kWave && k <= p.n_ckpt && r >= 0 && r < I.n)
+        __builtin_nontemporal_store(m.out[s][l],
+                                    p.ckpt + I.qoff * p.n_ckpt + (int64_t)(k - 1) * I.n + r);
+      k += kWave / kColsRows;
+    }
+  }
+}
+
+template <int C, int KIND, bool CKPT, typename V>
+__device__ __forceinline__ void cols_item(const ColsParams& p, ColsItem& I, ColsLds<V>& m,
+                                          ColsLds<V>* prev) {
+  using In = typename Val<V>::In;
+  const In* __restrict__ qa = reinterpret_cast<const In*>(p.queries) + I.qoff;
+  // second query of a binary16 pair (the same one at the end of an odd batch)
+  const In* __restrict__ qb = (Val<V>::N > 1 && I.b + 1 < p.batch) ? qa + I.n : qa;
+  const In* __restrict__ r = reinterpret_cast<const In*>(p.reference);
+  ColsLane<C, V> L;
+  const int j0 = I.cs + I.lane * C;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    L.rv[c] = Val<V>::ref(j0 + c < p.ref_len ? r[j0 + c] : In(0));
+    L.d[c] = Val<V>::zero();                           // row 0
+  }
+  L.shp = Val<V>::zero();
+  L.qv = Val<V>::zero();
+  L.tau = 0.0f;
+  if constexpr (KIND == kPruned) L.tau = vgpr_copy(p.prune_tau);
+  // (wait for the reference values here, not in the step loop)
+#pragma unroll
+  for (int c = 0; c < C; ++c) in_register(L.rv[c]);
+  I.ck_stride = I.ck_first = kWave;
+  I.ck_k = 0;
+  if constexpr (CKPT) {
+    // lanes whose last column is a checkpoint column (ckpt_every is a
+    // multiple of C, the segment need not be one of ckpt_every)
+    I.ck_stride = p.ckpt_every / C;
+    I.ck_first = (p.ckpt_every - I.cs % p.ckpt_every) / C - 1;
+    I.ck_k = (I.cs + (I.ck_first + 1) * C) / p.ckpt_every;
+  }
+
+  ColsStage<V> st;
+  st.load(I, qa, qb, 0);
+  st.commit(I, m, prev, 0);
+  wave_fence();
+  const int steps = I.n + kWave - 1;
+  for (int g0 = 0; g0 < steps; g0 += kColsRows) {
+    st.load(I, qa, qb, g0 + kColsRows);
+    const bool inside = g0 >= kWave && g0 + kColsRows <= I.n;  // every lane in rows 1..n
+    // (a multiple of kRowCkpt among rows g0 - 62 .. g0 + 8)
+    const bool rowck = CKPT && (g0 + kColsRows) / kRowCkpt != (g0 - kWave + 1) / kRowCkpt;
+    if (!inside) {
+      cols_group<C, KIND, CKPT, true, V>(p, I, L, m, g0);
+    } else if (rowck) {
+      if constexpr (CKPT) cols_group<C, KIND, true, false, V>(p, I, L, m, g0);
+    } else {
+      cols_group<C, KIND, false, false, V>(p, I, L, m, g0);
+    }
+    wave_fence();
+    cols_publish<C, CKPT, V>(p, I, m, g0);
+    st.commit(I, m, prev, g0 + kColsRows);
+    wave_fence();
+  }
+
+  // row n: every lane's d[] holds its columns' values.  The segment's
+  // minimum is combined with the running one of the segments before (first
+  // minimiser: a later segment wins only with a smaller value), which
+  // travels like the edge; the last segment stores the result.
+#pragma unroll
+  for (int h = 0; h < Val<V>::N; ++h) {
+    ValIdx am{inf_f32(), 0};
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const float v = Val<V>::half(L.d[c], h);
+      if (j0 + c < p.ref_len && v < am.v) am = ValIdx{v, j0 + c};
+    }
+    am = wave_argmin(am);
+    unsigned long long* x = I.edge + I.n + 2 * h;
+    if (I.seg > 0) {
+      unsigned long long a, b;
+      for (;;) {
+        a = edge_get(x);
+        b = edge_get(x + 1);
+        if ((uint32_t)(a >> 32) == (uint32_t)(I.seg - 1) &&
+            (uint32_t)(b >> 32) == (uint32_t)(I.seg - 1))
+          break;
+        __builtin_amdgcn_s_sleep(2);
+      }
+      const float pv = __builtin_bit_cast(float, (uint32_t)a);
+      if (!(am.v < pv)) am = ValIdx{pv, (int32_t)(uint32_t)b};
+    }
+    if (I.seg + 1 < I.nseg) {
+      if (I.lane == 0) {
+        edge_put(x, __builtin_bit_cast(uint32_t, am.v), I.seg);
+        edge_put(x + 1, (uint32_t)am.i, I.seg);
+      }
+    } else if (h == 0 || I.b + h < p.batch) {
+      p.cost[I.b + h] = am.v;                          // (the same value in every lane)
+      p.end_pos[I.b + h] = am.i;
+    }
+  }
+}
+
+template <int C, int KIND, bool CKPT, typename V>
+__global__ __launch_bounds__(kColsThreads) void sdtw_cols_kernel(const ColsParams p) {
+  __shared__ __attribute__((aligned(16))) ColsLds<V> mem[kColsWaves];
+  __shared__ ColsTickets tickets;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  ColsItem I;
+  I.lane = threadIdx.x & (kWave - 1);
+  I.nseg = p.nseg;
+  mem[w].put = 0;
+  mem[w].got = 0;
+  tickets.started[w] = 0;
+  if (w == 0) {
+    for (int k = 0; k < kColsTickets; ++k) tickets.ready[k] = 0;
+  }
+  __syncthreads();
+  // Without a counter (a single segment) every wavefront takes one query; with
+  // one, a workgroup's wavefronts take kColsWaves segments of a query.
+  const bool alone = p.queue == nullptr;
+  const int64_t groups = alone ? 1 : (p.nseg + kColsWaves - 1) / kColsWaves;
+  const int64_t items = (int64_t)p.units * groups;
+  uint32_t in_base = 0, out_base = 0;
+  for (uint32_t k = 0;; ++k) {
+    int64_t item;
+    if (alone) {
+      item = k == 0 ? (int64_t)blockIdx.x * kColsWaves + w : items;
+    } else {
+      uint32_t* ready = &tickets.ready[k % kColsTickets];
+      int64_t* slot = &tickets.item[k % kColsTickets];
+      if (w == 0) {
+        for (int o = 1; o < kColsWaves; ++o)
+          while ((int32_t)(k - lds_get(&tickets.started[o])) >= kColsTickets)
+            __builtin_amdgcn_s_sleep(1);
+        // (every lane takes part, lane 0 adds 1: no lane-dependent branch)
+        item = uniform64((int64_t)atomicAdd(p.queue, I.lane == 0 ? 1ull : 0ull));
+        *slot = item;
+        lds_put(ready, k + 1);
+      } else {
+        while (lds_get(ready) != k + 1) __builtin_amdgcn_s_sleep(1);
+        item = uniform64(*slot);
+        lds_put(&tickets.started[w], k + 1);
+      }
+    }
+    if (item >= items) break;
+    const int group = (int)(item / p.units);
+    I.seg = alone ? 0 : group * kColsWaves + w;
+    I.b = (int)(item - (int64_t)group * p.units) * Val<V>::N;
+    if (I.seg >= p.nseg) continue;             // (the query's last, partial item)
+    I.n = __builtin_amdgcn_readfirstlane(p.lens[I.b]);
+    I.cs = I.seg * kWave * C;
+    I.from_lds = !alone && w > 0;
+    I.to_lds = !alone && w + 1 < kColsWaves && I.seg + 1 < p.nseg;
+    I.in_base = in_base;
+    I.out_base = out_base;
+    if (p.offsets != nullptr) {
+      I.qoff = uniform64(p.offsets[I.b]);
+    } else {
+      int64_t acc = 0;
+      for (int j = I.lane; j < I.b; j += kWave) acc += p.lens[j];
+      for (int d = kWave / 2; d > 0; d >>= 1) acc += __shfl_xor(acc, d);
+      I.qoff = uniform64(acc);
+    }
+    I.edge = p.edges + I.qoff + kColsExtra * (int64_t)I.b;
+    cols_item<C, KIND, CKPT, V>(p, I, mem[w], w > 0 ? &mem[w - 1] : nullptr);
+    if (I.from_lds) in_base += (uint32_t)I.n;
+    if (I.to_lds) out_base += (uint32_t)I.n;
+  }
+}
+
+}  // namespace sdtw

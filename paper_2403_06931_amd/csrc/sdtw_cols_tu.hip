@@ -1,0 +1,40 @@
+// sdtw_cols_tu.hip -- the column-owning forward (sdtw_cols.hpp) as an entry of
+// the variant table, compiled by the build script as variant
+// SDTW_VARIANT_INDEX.
+#include "sdtw_cols.hpp"
+#include "sdtw_variant.hpp"
+
+#define SDTW_CAT2(a, b) a##b
+#define SDTW_CAT(a, b) SDTW_CAT2(a, b)
+
+namespace {
+
+template <int C, int KIND, bool CKPT, typename V>
+const void* entry() {
+  return reinterpret_cast<const void*>(&sdtw::sdtw_cols_kernel<C, KIND, CKPT, V>);
+}
+
+}  // namespace
+
+// (one row per step, T W columns per lane; every launch is the persistent
+// form, so both entries name the same kernel)
+sdtw::Variant SDTW_CAT(sdtw_variant_entry_, SDTW_VARIANT_INDEX)() {
+  constexpr int C = SDTW_T * SDTW_W;
+  sdtw::Variant v{};
+  v.R = SDTW_R;
+  v.T = SDTW_T;
+  v.W = SDTW_W;
+  v.KS = SDTW_KS;
+  v.XL = SDTW_XL;
+  v.cols = C;
+  v.plain[0][0] = v.persistent[0][0] = entry<C, 0, false, float>();
+  v.plain[0][1] = v.persistent[0][1] = entry<C, 0, true, float>();
+  v.plain[1][0] = v.persistent[1][0] = entry<C, 1, false, float>();
+  v.plain[1][1] = v.persistent[1][1] = entry<C, 1, true, float>();
+  v.pruned[0] = v.pruned[1] = entry<C, sdtw::kPruned, false, float>();
+  v.u8 = entry<C, 0, false, sdtw::Code8>();
+  v.half[0] = entry<C, 0, false, sdtw::f16x2>();
+  v.half[1] = entry<C, 1, false, sdtw::f16x2>();
+  v.lds_bytes = (int)(sizeof(sdtw::ColsLds<float>) * (sdtw::kColsThreads / sdtw::kWave));
+  return v;
+}

@@ -1,6 +1,6 @@
 // sdtw_setup.hpp -- small one-workgroup kernels that run before the DP
-// kernels: the query offset table and the processing order of the
-// persistent form.  Included by the API translation unit only.
+// kernels: the query offset table, the processing order of the persistent
+// form and the column-owning form's counter and edge words.  Included by the API translation unit only.
 #pragma once
 
 #include "sdtw_common.hpp"
@@ -102,6 +102,42 @@ __global__ __launch_bounds__(kScanThreads) void sdtw_order_kernel(
     const int at = atomicAdd(&s_cnt[kOrderBins - 1 - key], 1);
     order[at] = b;
   }
+}
+
+// Before the columns kernel: offsets of the queries (workgroup 0, as
+// sdtw_offsets_kernel) and the item counter; the other workgroups mark every
+// edge word as belonging to no segment.
+__global__ __launch_bounds__(kScanThreads) void sdtw_cols_init_kernel(
+    const int32_t* __restrict__ lens, int32_t batch, int64_t* __restrict__ offsets,
+    unsigned long long* __restrict__ queue, unsigned long long* __restrict__ edges,
+    int64_t words) {
+  const int tid = threadIdx.x;
+  if (blockIdx.x > 0) {
+    const int64_t stride = (int64_t)(gridDim.x - 1) * kScanThreads;
+    for (int64_t i = (int64_t)(blockIdx.x - 1) * kScanThreads + tid; i < words; i += stride)
+      edges[i] = ~0ull;
+    return;
+  }
+  __shared__ int64_t s_sum[kScanThreads];
+  if (tid == 0) queue[0] = 0;
+  const int per = (batch + kScanThreads - 1) / kScanThreads;
+  const int lo = min(batch, tid * per), hi = min(batch, lo + per);
+  int64_t acc = 0;
+  for (int i = lo; i < hi; ++i) acc += lens[i];
+  s_sum[tid] = acc;
+  __syncthreads();
+  for (int d = 1; d < kScanThreads; d <<= 1) {
+    const int64_t v = tid >= d ? s_sum[tid - d] : 0;
+    __syncthreads();
+    s_sum[tid] += v;
+    __syncthreads();
+  }
+  int64_t run = s_sum[tid] - acc;
+  for (int i = lo; i < hi; ++i) {
+    offsets[i] = run;
+    run += lens[i];
+  }
+  if (tid == kScanThreads - 1) offsets[batch] = s_sum[tid];
 }
 
 }  // namespace sdtw

@@ -15,11 +15,12 @@ struct Variant {
   const void* pruned[2];          // squared cost with early pruning: [plain, persistent]
   const void* u8;                 // integer DP on uint8 codes
   int lds_bytes;
+  int cols;                       // lanes own this many columns (sdtw_cols.hpp); 0: rows
 };
 
 template <int R, int T, int W, int KS, int XL>
 Variant make_variant() {
-  Variant v;
+  Variant v{};
   v.R = R;
   v.T = T;
   v.W = W;
