@@ -358,11 +358,15 @@ int pick_variant(const int32_t* h_lens, int32_t batch, int64_t ref_len, int32_t 
 // both are kept under kBwdCodeBudget bytes where the batch allows, with at
 // least one block per round.
 constexpr size_t kBwdCodeBudget = size_t(2) << 30;
+constexpr size_t kBwdCodeBudgetFew = size_t(512) << 20;   // for more than kBwdMaxSlots blocks
 // Round kernels from this one on recompute their blocks as row bands.  The
 // first two recomputes (rounds 0 and 1: every query's first blocks, then
 // those of nearly every query, since round 1's are started before round 0's
-// walk ends) are bound by issue slots, where bands would only add pipeline
-// fill and more wavefronts beside the walkers: whole blocks there.
+// walk ends) are bound by issue slots in a batch that fills the chip, where
+// bands would only add pipeline fill and more wavefronts beside the walkers:
+// whole blocks there.  A batch whose bands are at most two wavefronts per
+// SIMD is bound by one wavefront's chain from the start: bands in every
+// round, and up to kBwdMaxSlotsFew blocks per round (fewer rounds).
 constexpr int kFirstBandedKernel = 1;
 // Band height, a multiple of the row-checkpoint spacing.  (On 256 x 1,000
 // vs 50,000, bands of 512 rows in the first banded kernel and 256 after it
@@ -376,11 +380,13 @@ struct BwdLayout {
   size_t offsets, state, lo, row_lo, row_hi, part, codes, total;
   int64_t code_half;          // words per code buffer
   int32_t nseg, slots, rounds;
+  bool few;                  // bands of every round leave SIMDs idle
 };
 
+
 // with_grad = false (sdtw_align): no per-query reference partials.
-BwdLayout bwd_layout(int32_t batch, int64_t total_len, int64_t ref_len, int32_t ckpt_every,
-                     bool with_grad = true) {
+BwdLayout bwd_layout(int32_t batch, int64_t total_len, int32_t nmax, int64_t ref_len,
+                     int32_t ckpt_every, bool with_grad = true) {
   BwdLayout L{};
   L.nseg = (ckpt_every + sdtw::kDirSeg - 1) / sdtw::kDirSeg;
   const size_t words_per_slot =
@@ -389,6 +395,16 @@ BwdLayout bwd_layout(int32_t batch, int64_t total_len, int64_t ref_len, int32_t 
   const int64_t nblk = (ref_len + ckpt_every - 1) / ckpt_every;
   int64_t slots = (int64_t)(kBwdCodeBudget / (2 * bytes_per_slot));
   slots = std::max<int64_t>(1, std::min<int64_t>({slots, sdtw::kBwdMaxSlots, nblk}));
+  const int64_t nband = nblk > 1 ? (nmax + kBandRows - 1) / kBandRows : 1;
+  const int64_t idle_waves = 8LL * device_cus();          // two wavefronts per SIMD
+  L.few = (int64_t)batch * slots * nband <= idle_waves;
+  while (L.few && slots < std::min<int64_t>(nblk, sdtw::kBwdMaxSlotsFew)) {
+    const int64_t more = std::min<int64_t>({2 * slots, nblk, sdtw::kBwdMaxSlotsFew});
+    if ((int64_t)batch * more * nband > idle_waves ||
+        2 * bytes_per_slot * (size_t)more > kBwdCodeBudgetFew)
+      break;
+    slots = more;
+  }
   L.slots = (int32_t)slots;
   L.rounds = (int32_t)((nblk + slots - 1) / slots);
   size_t at = 0;
@@ -556,24 +572,13 @@ sdtw::BwdParams bwd_params(const float* queries, const int32_t* query_lens, int3
 // The walk itself: offsets, walker state, round 0's recompute, then the
 // rounds (walk of round r beside the recompute of round r+1).  Leaves the
 // path bounds in p.row_lo, p.row_hi and p.path_lo.
-int bwd_walk(sdtw::BwdParams& p, const BwdLayout& L, const int32_t* query_lens, int32_t batch,
-             int32_t nmax, bool sq, hipStream_t stream) {
-  int64_t* offs = const_cast<int64_t*>(p.offsets);
-  int rc;
+int bwd_walk(sdtw::BwdParams& p, const BwdLayout& L, int32_t batch, int32_t nmax, bool sq,
+             hipStream_t stream) {
   {
-    int32_t rows = 0;
-    int32_t* ranks = nullptr;
-    void* args[] = {(void*)&query_lens, (void*)&batch, (void*)&offs, (void*)&rows,
-                    (void*)&ranks};
-    rc = launch(reinterpret_cast<const void*>(&sdtw::sdtw_offsets_kernel), dim3(1),
-                dim3(sdtw::kScanThreads), args, stream);
-    if (rc != SDTW_OK) return rc;
-  }
-  {
-    void* args[] = {(void*)&p};
-    rc = launch(reinterpret_cast<const void*>(&sdtw::sdtw_bwd_init_kernel),
-                dim3((batch + sdtw::kInitThreads - 1) / sdtw::kInitThreads),
-                dim3(sdtw::kInitThreads), args, stream);
+    int64_t* offs = const_cast<int64_t*>(p.offsets);
+    void* args[] = {(void*)&p, (void*)&offs};
+    const int rc = launch(reinterpret_cast<const void*>(&sdtw::sdtw_bwd_setup_kernel), dim3(1),
+                          dim3(sdtw::kBwdSetupThreads), args, stream);
     if (rc != SDTW_OK) return rc;
   }
   const size_t round_lds = sdtw::bwd_round_lds_bytes(nmax);      // per wavefront
@@ -587,12 +592,13 @@ int bwd_walk(sdtw::BwdParams& p, const BwdLayout& L, const int32_t* query_lens, 
   {
     const void* dirs = sq ? reinterpret_cast<const void*>(&sdtw::sdtw_bwd_dirs_kernel<0>)
                           : reinterpret_cast<const void*>(&sdtw::sdtw_bwd_dirs_kernel<1>);
-    p.nband = 1;
+    p.band_rows = kBandRows;
+    p.nband = L.few ? bands(p.band_rows) : 1;
     // up to four wavefronts per workgroup, each with its own query and left
     // column in LDS (at most 64 KB per workgroup)
     const size_t per_wave = sizeof(float) * 2 * (size_t)nmax;
     const int wpg = (int)std::max<size_t>(1, std::min<size_t>(4, 65536 / per_wave));
-    const int64_t items = (int64_t)batch * L.slots;
+    const int64_t items = (int64_t)batch * L.slots * p.nband;
     void* args[] = {(void*)&p};
     if (hipLaunchKernel(dirs, dim3((unsigned)((items + wpg - 1) / wpg)), dim3(sdtw::kWave * wpg),
                         args, per_wave * wpg, stream) != hipSuccess)
@@ -604,7 +610,7 @@ int bwd_walk(sdtw::BwdParams& p, const BwdLayout& L, const int32_t* query_lens, 
     p.round = r;
     // (no next round: no recompute wavefronts, padding ones included)
     p.band_rows = kBandRows;
-    p.nband = r + 1 == L.rounds ? 0 : (r >= kFirstBandedKernel ? bands(p.band_rows) : 1);
+    p.nband = r + 1 == L.rounds ? 0 : (L.few || r >= kFirstBandedKernel ? bands(p.band_rows) : 1);
     const int64_t grid = (int64_t)batch * (1 + (int64_t)L.slots * p.nband);
     void* args[] = {(void*)&p};
     if (hipLaunchKernel(round_fn, dim3((unsigned)((grid + round_wpg - 1) / round_wpg)),
@@ -979,7 +985,7 @@ size_t sdtw_backward_workspace_bytes(const int32_t* h_query_lens, int32_t batch,
       ckpt_every % kCkptQuantum != 0)
     return 0;
   if (nmax > sdtw::kDirMaxRows) return 0;
-  return bwd_layout(batch, total, ref_len, ckpt_every).total;
+  return bwd_layout(batch, total, nmax, ref_len, ckpt_every).total;
 }
 
 int sdtw_backward(const float* queries, const int32_t* h_query_lens, const int32_t* query_lens,
@@ -1002,7 +1008,7 @@ int sdtw_backward(const float* queries, const int32_t* h_query_lens, const int32
   if (nck > 0 && ckpt == nullptr) return SDTW_ERR_INVALID_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0) return SDTW_ERR_INVALID_ARG;
   if (nmax > sdtw::kDirMaxRows) return SDTW_ERR_UNSUPPORTED;
-  const BwdLayout L = bwd_layout(batch, total, ref_len, ckpt_every);
+  const BwdLayout L = bwd_layout(batch, total, nmax, ref_len, ckpt_every);
   if (workspace_bytes < L.total) return SDTW_ERR_WORKSPACE;
 
   hipStream_t stream = reinterpret_cast<hipStream_t>(stream_ptr);
@@ -1011,7 +1017,7 @@ int sdtw_backward(const float* queries, const int32_t* h_query_lens, const int32
   p.grad_cost = grad_cost;
   p.grad_q = grad_queries;
   const bool sq = cost_kind == SDTW_COST_SQUARED;
-  const int rc = bwd_walk(p, L, query_lens, batch, nmax, sq, stream);
+  const int rc = bwd_walk(p, L, batch, nmax, sq, stream);
   if (rc != SDTW_OK) return rc;
   {
     const bool qlds = sdtw::bwd_grad_q_in_lds(nmax);
@@ -1047,7 +1053,7 @@ size_t sdtw_align_workspace_bytes(const int32_t* h_query_lens, int32_t batch, in
       ckpt_every % kCkptQuantum != 0)
     return 0;
   if (nmax > sdtw::kDirMaxRows) return 0;
-  return bwd_layout(batch, total, ref_len, ckpt_every, false).total;
+  return bwd_layout(batch, total, nmax, ref_len, ckpt_every, false).total;
 }
 
 int sdtw_align(const float* queries, const int32_t* h_query_lens, const int32_t* query_lens,
@@ -1069,7 +1075,7 @@ int sdtw_align(const float* queries, const int32_t* h_query_lens, const int32_t*
   if (nck > 0 && ckpt == nullptr) return SDTW_ERR_INVALID_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0) return SDTW_ERR_INVALID_ARG;
   if (nmax > sdtw::kDirMaxRows) return SDTW_ERR_UNSUPPORTED;
-  const BwdLayout L = bwd_layout(batch, total, ref_len, ckpt_every, false);
+  const BwdLayout L = bwd_layout(batch, total, nmax, ref_len, ckpt_every, false);
   if (workspace_bytes < L.total) return SDTW_ERR_WORKSPACE;
 
   hipStream_t stream = reinterpret_cast<hipStream_t>(stream_ptr);
@@ -1078,7 +1084,7 @@ int sdtw_align(const float* queries, const int32_t* h_query_lens, const int32_t*
   p.ref_part = nullptr;
   p.row_lo = path_lo;                           // the walker writes the bounds in place
   p.row_hi = path_hi;
-  const int rc = bwd_walk(p, L, query_lens, batch, nmax, cost_kind == SDTW_COST_SQUARED, stream);
+  const int rc = bwd_walk(p, L, batch, nmax, cost_kind == SDTW_COST_SQUARED, stream);
   if (rc != SDTW_OK) return rc;
   const int32_t* lo = p.path_lo;
   void* args[] = {(void*)&lo, (void*)&batch, (void*)&start_pos};

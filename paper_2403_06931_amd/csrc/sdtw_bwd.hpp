@@ -45,7 +45,8 @@ constexpr int kDirCols = 16;                    // reference columns per lane
 constexpr int kDirSeg = kWave * kDirCols;       // columns per segment
 constexpr int kDirMaxRows = 8192;               // query + left column held in LDS
 constexpr int kWalkChunk = 32;                  // code rows per walker LDS chunk
-constexpr int kBwdMaxSlots = 8;                 // blocks per round per query
+constexpr int kBwdMaxSlots = 8;                 // blocks per round per query,
+constexpr int kBwdMaxSlotsFew = 32;             // of a batch that leaves SIMDs idle
 
 // Direction code of a cell, 2 bits: a = "the diagonal is not a minimum",
 // u = "the cell above is not a minimum".  The walk steps diagonally if a is
@@ -134,19 +135,40 @@ __device__ __forceinline__ float dcost_dq(float q, float r) {
   }
 }
 
-// Walker state: start at (N, end_pos); row N's last path column is end_pos.
+// One workgroup: the queries' offsets (a scan of their lengths) and the
+// walkers' state: start at (N, end_pos); row N's last path column is end_pos.
 constexpr int kInitThreads = 256;
+constexpr int kBwdSetupThreads = 1024;
 
-__global__ __launch_bounds__(kInitThreads) void sdtw_bwd_init_kernel(const BwdParams p) {
-  const int b = blockIdx.x * kInitThreads + threadIdx.x;
-  if (b >= p.batch) return;
-  const int n = p.lens[b];
-  const int e = (int)p.end_pos[b];
-  p.state[4 * b + 0] = n;
-  p.state[4 * b + 1] = e;
-  p.state[4 * b + 2] = 0;
-  p.state[4 * b + 3] = 0;
-  p.row_hi[p.offsets[b] + n - 1] = e;
+__global__ __launch_bounds__(kBwdSetupThreads) void sdtw_bwd_setup_kernel(
+    const BwdParams p, int64_t* __restrict__ offsets) {
+  __shared__ int64_t s_sum[kBwdSetupThreads];
+  const int tid = threadIdx.x;
+  const int per = (p.batch + kBwdSetupThreads - 1) / kBwdSetupThreads;
+  const int lo = min(p.batch, tid * per), hi = min(p.batch, lo + per);
+  int64_t acc = 0;
+  for (int b = lo; b < hi; ++b) acc += p.lens[b];
+  s_sum[tid] = acc;
+  __syncthreads();
+  for (int d = 1; d < kBwdSetupThreads; d <<= 1) {
+    const int64_t v = tid >= d ? s_sum[tid - d] : 0;
+    __syncthreads();
+    s_sum[tid] += v;
+    __syncthreads();
+  }
+  int64_t run = s_sum[tid] - acc;
+  for (int b = lo; b < hi; ++b) {
+    const int n = p.lens[b];
+    const int e = (int)p.end_pos[b];
+    offsets[b] = run;
+    run += n;
+    p.state[4 * b + 0] = n;
+    p.state[4 * b + 1] = e;
+    p.state[4 * b + 2] = 0;
+    p.state[4 * b + 3] = 0;
+    p.row_hi[run - 1] = e;
+  }
+  if (tid == kBwdSetupThreads - 1) offsets[p.batch] = s_sum[tid];
 }
 
 // Start of each query's path (the column of its row-1 cell), widened to the
@@ -173,8 +195,10 @@ __device__ __forceinline__ void dirs_step(int g, int lane, int nrows, float il, 
                                           float* ledge, const float (&rv)[kDirCols],
                                           float (&dprev)[kDirCols], float& last, float& shp,
                                           float& qv, uint32_t* __restrict__ out, int64_t rs) {
-  const float shc = wave_shr1(il, last);          // left neighbour on this row
-  qv = wave_shr1(iq, qv);                         // this row's query value
+  // left neighbour on this row and this row's query value
+  float shc = il, q = iq;
+  wave_shr1_pair(shc, last, q, qv);
+  qv = q;
   float cur[kDirCols];
   uint32_t word = 0;
   float left = shc, diag = shp;
@@ -450,10 +474,10 @@ __host__ __device__ constexpr size_t bwd_round_lds_bytes(int max_rows) {
              : sizeof(uint32_t) * kWalkChunk * kWave;
 }
 
-// Round 0's blocks, one wavefront each, blockDim.x / 64 wavefronts per
-// workgroup (each with its own 2 * max_rows floats of LDS): block item
+// Round 0's blocks (row bands), one wavefront each, blockDim.x / 64 wavefronts
+// per workgroup (each with its own 2 * max_rows floats of LDS): item
 // e = blockIdx.x * (blockDim.x / 64) + wave is query e % batch, slot
-// e / batch.  (Several wavefronts per workgroup keep the placement even: a
+// e / batch / nband, band e / batch % nband.  (Several wavefronts per workgroup keep the placement even: a
 // grid of as many one-wavefront workgroups as two per SIMD was placed
 // unevenly depending on the kernel before it, up to 1.4 times slower.)
 template <int KIND>
@@ -461,8 +485,10 @@ __global__ __launch_bounds__(4 * kWave) void sdtw_bwd_dirs_kernel(const BwdParam
   extern __shared__ __attribute__((aligned(16))) float dyn[];
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int e = (int)blockIdx.x * (int)(blockDim.x / kWave) + w;
-  if (e >= p.batch * p.slots) return;
-  dirs_block<KIND>(p, 0, e % p.batch, e / p.batch, 0, dyn + (size_t)w * 2 * p.max_rows);
+  const int tz = e / p.batch;
+  if (tz >= p.slots * p.nband) return;
+  dirs_block<KIND>(p, 0, e % p.batch, tz / p.nband, tz % p.nband,
+                   dyn + (size_t)w * 2 * p.max_rows);
 }
 
 // Round r = p.round: wavefronts [0, batch) walk round r; when another round
