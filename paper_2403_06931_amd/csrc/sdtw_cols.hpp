@@ -380,6 +380,9 @@ __device__ __forceinline__ void cols_item(const ColsParams& p, ColsItem& I, Cols
         edge_put(x + 1, (uint32_t)am.i, I.seg);
       }
     } else if (h == 0 || I.b + h < p.batch) {
+      if constexpr (Val<V>::N > 1) {
+        if (any_infinite<V>(h == 0 ? qa : qb, I.n)) am = ValIdx{inf_f32(), 0};
+      }
       p.cost[I.b + h] = am.v;                          // (the same value in every lane)
       p.end_pos[I.b + h] = am.i;
     }

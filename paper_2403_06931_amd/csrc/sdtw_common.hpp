@@ -71,6 +71,38 @@ __device__ __forceinline__ void in_register(X& x) {
   }
 }
 
+// One tile row of T lane values between registers and LDS, four at a time,
+// in planes of four columns STRIDE words apart (4 for a row stored in one
+// piece); every piece is 16-byte aligned.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <int STRIDE>
+__device__ __forceinline__ int plane_at(int x, int t) {
+  return (t >> 2) * STRIDE + 4 * x + (t & 3);
+}
+
+template <int T, int STRIDE, typename V>
+__device__ __forceinline__ void tile_load(V (&dst)[T], const V* src) {
+  static_assert(T % 4 == 0 && sizeof(V) == 4, "16-byte pieces");
+#pragma unroll
+  for (int t = 0; t < T; t += 4) {
+    const u32x4 w = *reinterpret_cast<const u32x4*>(src + (t / 4) * STRIDE);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) dst[t + u] = __builtin_bit_cast(V, (uint32_t)w[u]);
+  }
+}
+
+template <int T, int STRIDE, typename V>
+__device__ __forceinline__ void tile_store(V* dst, const V (&src)[T]) {
+#pragma unroll
+  for (int t = 0; t < T; t += 4) {
+    u32x4 w;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) w[u] = __builtin_bit_cast(uint32_t, src[t + u]);
+    *reinterpret_cast<u32x4*>(dst + (t / 4) * STRIDE) = w;
+  }
+}
+
 // Exact three-way minimum (one v_min3_f32).  Inputs are never NaN here: DP
 // values start at 0 or +inf and every LDS slot a lane reads before its
 // first tile is initialised (+inf boundaries, a zeroed reference ring).

@@ -124,38 +124,6 @@ struct FwdShape {
   static constexpr int lds_floats() { return LDS_FLOATS + (CKPT ? MIDRING : 0); }
 };
 
-// One tile row of T lane values between registers and LDS, four at a time,
-// in planes of four columns STRIDE words apart (4 for a row stored in one
-// piece); every piece is 16-byte aligned.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-template <int STRIDE>
-__device__ __forceinline__ int plane_at(int x, int t) {
-  return (t >> 2) * STRIDE + 4 * x + (t & 3);
-}
-
-template <int T, int STRIDE, typename V>
-__device__ __forceinline__ void tile_load(V (&dst)[T], const V* src) {
-  static_assert(T % 4 == 0 && sizeof(V) == 4, "16-byte pieces");
-#pragma unroll
-  for (int t = 0; t < T; t += 4) {
-    const u32x4 w = *reinterpret_cast<const u32x4*>(src + (t / 4) * STRIDE);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) dst[t + u] = __builtin_bit_cast(V, (uint32_t)w[u]);
-  }
-}
-
-template <int T, int STRIDE, typename V>
-__device__ __forceinline__ void tile_store(V* dst, const V (&src)[T]) {
-#pragma unroll
-  for (int t = 0; t < T; t += 4) {
-    u32x4 w;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) w[u] = __builtin_bit_cast(uint32_t, src[t + u]);
-    *reinterpret_cast<u32x4*>(dst + (t / 4) * STRIDE) = w;
-  }
-}
-
 // Stage the reference tiles [tile0, tile0 + KS) and the wave-0 top boundary
 // (zeros on the first pass, the previous pass's last row after it) from
 // global memory into registers; commit them to the LDS rings later.
@@ -391,34 +359,8 @@ __device__ __forceinline__ void fwd_step(const FwdParams& p, LaneState<R, T, V>&
   using S = FwdShape<R, T, W, KS, XL>;
   V upleft = L.corner;                          // D(row-1, first col - 1)
   L.corner = up[T - 1];
-  if constexpr (Val<V>::kAntiDiagonal) {
-    // Anti-diagonal order (packed binary16): gfx950 needs a wait state
-    // between dependent packed instructions; cells (k, t) and (k+1, t-1)
-    // are independent, so this order puts independent work between them.
-    V D[R][T];
-#pragma unroll
-    for (int d = 0; d < R + T - 1; ++d) {
-#pragma unroll
-      for (int k = 0; k < R; ++k) {
-        const int t = d - k;
-        if (t < 0 || t >= T) continue;
-        const V u = k == 0 ? up[t] : D[k - 1][t];
-        const V lf = t == 0 ? L.dl[k] : D[k][t - 1];
-        const V dg = t == 0 ? (k == 0 ? upleft : L.dl[k - 1]) : (k == 0 ? up[t - 1] : D[k - 1][t - 1]);
-        D[k][t] = Val<V>::template cell<KIND>(L.qv[k], rv[t], u, lf, dg, L.tau);
-      }
-    }
-    if constexpr (OUTK >= 0 && OUTK < R - 1) {
-#pragma unroll
-      for (int t = 0; t < T; ++t) outv[t] = D[OUTK][t];
-    }
-#pragma unroll
-    for (int k = 0; k < R; ++k) L.dl[k] = D[k][T - 1];
-#pragma unroll
-    for (int t = 0; t < T; ++t) up[t] = D[R - 1][t];
-  } else {
-  // The block row by row (measured faster on gfx950 than anti-diagonal
-  // order, which the compiler schedules worse for dual issue).
+  // The block row by row (anti-diagonal order, which the compiler schedules
+  // worse for dual issue, measured slower for every value type).
 #pragma unroll
   for (int k = 0; k < R; ++k) {
     V left = L.dl[k];
@@ -438,7 +380,6 @@ __device__ __forceinline__ void fwd_step(const FwdParams& p, LaneState<R, T, V>&
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) up[t] = cur[t];
-  }
   }
 #pragma unroll
   for (int t = 0; t < T; ++t) L.bot[t] = up[t];
@@ -796,7 +737,10 @@ __device__ __forceinline__ void fwd_one_pass(const FwdParams& p, int b, PassGeom
 #pragma unroll
       for (int h = 0; h < Val<V>::N; ++h) {
         if (h == 0 || b + h < p.batch) {
-          const ValIdx x = wave_argmin(L.am[h]);
+          ValIdx x = wave_argmin(L.am[h]);
+          if constexpr (Val<V>::N > 1) {
+            if (any_infinite<V>(h == 0 ? q : q2, G.n)) x = ValIdx{inf_f32(), 0};
+          }
           p.cost[b + h] = x.v;
           p.end_pos[b + h] = x.i;
         }

@@ -21,7 +21,6 @@
 namespace sdtw {
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 template <typename V>
 struct Val;
@@ -30,7 +29,6 @@ template <>
 struct Val<float> {
   using In = float;                            // element type in HBM
   static constexpr int N = 1;                  // queries per value
-  static constexpr bool kAntiDiagonal = false; // cell order in a step's block
   __device__ static float inf() { return inf_f32(); }
   __device__ static float zero() { return 0.0f; }
   __device__ static float query(float a, float) { return a; }
@@ -52,14 +50,20 @@ template <>
 struct Val<f16x2> {
   using In = float;
   static constexpr int N = 2;
-  static constexpr bool kAntiDiagonal = true;
   __device__ static f16x2 inf() {
     const _Float16 h = (_Float16)__builtin_huge_valf();
     return f16x2{h, h};
   }
   __device__ static f16x2 zero() { return f16x2{(_Float16)0.0f, (_Float16)0.0f}; }
-  // the two queries' values, rounded to binary16
-  __device__ static f16x2 query(float a, float b) { return f16x2{(_Float16)a, (_Float16)b}; }
+  // The two queries' values, rounded to binary16.  One that rounds to an
+  // infinity makes its query's every path cost +inf (no reference value is
+  // at a finite distance); it is replaced by 0 here and the query's result
+  // set when it is stored (infinite).
+  __device__ static _Float16 finite(float a) {
+    return infinite(a) ? (_Float16)0.0f : (_Float16)a;
+  }
+  __device__ static bool infinite(float a) { return __builtin_fabsf(a) >= 65520.0f; }
+  __device__ static f16x2 query(float a, float b) { return f16x2{finite(a), finite(b)}; }
   // one reference value for both halves
   __device__ static f16x2 ref(float r) {
     const _Float16 h = (_Float16)r;
@@ -76,16 +80,12 @@ struct Val<f16x2> {
       return __builtin_bit_cast(f16x2, __builtin_bit_cast(uint32_t, t) & 0x7fff7fffu);
     }
   }
-  // DP values are never negative or NaN, and the bit patterns of binary16
-  // values >= +0 (up to +inf) order like the values, so an unsigned 16-bit
-  // minimum per half is the exact minimum (v_pk_min_u16; a floating-point
-  // minimum would first have to quiet signalling NaNs, an extra instruction
-  // per operand that comes from memory or a lane move).
+  // v_pk_minimum3_f16: one instruction for both halves.  It hands a NaN on,
+  // but none arises from inputs that are not NaN: query values are finite
+  // (above), so a difference is never inf - inf, and DP values are never
+  // negative.
   __device__ static f16x2 min3(f16x2 a, f16x2 b, f16x2 c) {
-    const u16x2 m = __builtin_elementwise_min(
-        __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)),
-        __builtin_bit_cast(u16x2, c));
-    return __builtin_bit_cast(f16x2, m);
+    return __builtin_elementwise_minimum(__builtin_elementwise_minimum(a, b), c);
   }
   __device__ static f16x2 add(f16x2 a, f16x2 b) { return a + b; }          // v_pk_add_f16
   template <int KIND>
@@ -115,7 +115,6 @@ template <>
 struct Val<Code8> {
   using In = uint8_t;
   static constexpr int N = 1;
-  static constexpr bool kAntiDiagonal = false;  // measured: row order is as fast
   __device__ static Code8 inf() { return Code8{inf_f32()}; }
   __device__ static Code8 zero() { return Code8{0.0f}; }
   __device__ static Code8 query(uint8_t a, uint8_t) { return Code8{(float)a}; }
@@ -131,5 +130,15 @@ struct Val<Code8> {
   }
   __device__ static float half(Code8 v, int) { return v.v; }
 };
+
+// Whether one of a query's n values rounds to an infinity (binary16); the
+// same answer in every lane of the wavefront.
+template <typename V>
+__device__ __forceinline__ bool any_infinite(const float* q, int n) {
+  bool bad = false;
+  for (int k = (int)(threadIdx.x & (kWave - 1)); k < n; k += kWave)
+    bad = bad || Val<V>::infinite(q[k]);
+  return __ballot(bad) != 0;
+}
 
 }  // namespace sdtw
