@@ -88,13 +88,26 @@ __global__ __launch_bounds__(kScanThreads) void sdtw_order_kernel(
     atomicAdd(&s_cnt[kOrderBins - 1 - key], 1);        // descending by work
   }
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    for (int i = 0; i < kOrderBins; ++i) {
-      const int c = s_cnt[i];
-      s_cnt[i] = run;
-      run += c;
-    }
+  // exclusive scan of the bins, kOrderBins / kScanThreads of them per thread
+  // (one thread adding up all of them took longer than the DP of a small
+  // batch)
+  constexpr int PER = kOrderBins / kScanThreads;
+  __shared__ int32_t s_sum[kScanThreads];
+  int32_t mine = 0;
+  for (int i = 0; i < PER; ++i) mine += s_cnt[tid * PER + i];
+  s_sum[tid] = mine;
+  __syncthreads();
+  for (int d = 1; d < kScanThreads; d <<= 1) {
+    const int32_t v = tid >= d ? s_sum[tid - d] : 0;
+    __syncthreads();
+    s_sum[tid] += v;
+    __syncthreads();
+  }
+  int32_t run = s_sum[tid] - mine;
+  for (int i = 0; i < PER; ++i) {
+    const int32_t c = s_cnt[tid * PER + i];
+    s_cnt[tid * PER + i] = run;
+    run += c;
   }
   __syncthreads();
   for (int b = tid; b < batch; b += kScanThreads) {
