@@ -118,10 +118,10 @@ int64_t fwd_edge_words(const Variant& v, int64_t total_len, int32_t batch, int64
 }
 
 // uint8-code forward: the plain forward's workspace, then the codes of the
-// queries and of the reference, the per-chunk extremes and the codebook.
+// queries and of the reference and the per-chunk extremes.
 struct U8Layout {
   FwdLayout fwd;
-  size_t qcodes, rcodes, part, book, total;
+  size_t qcodes, rcodes, part, total;
   int nparts;
 };
 
@@ -137,8 +137,6 @@ U8Layout u8_layout(int32_t batch, int64_t total_rows, int64_t ref_len) {
   L.nparts = (int)((ref_len + sdtw::kQChunk - 1) / sdtw::kQChunk);
   L.part = at;
   at = align_up(at + sizeof(float2) * (size_t)L.nparts, kAlign);
-  L.book = at;
-  at = align_up(at + sizeof(sdtw::QBook), kAlign);
   L.total = at;
   return L;
 }
@@ -222,19 +220,20 @@ BatchShape batch_shape(const int32_t* h_lens, int32_t batch) {
 //
 // Column-owning form, C = 16 (32) columns per lane: a step takes 0.165
 // (0.275) us alone on its SIMD and 0.09 (0.20) us of a SIMD's time when it is
-// shared; a segment starts 18 (29) us behind the one before it.  So a few
+// shared; a segment starts 17.5 (27) us behind the one before it.  So a few
 // queries are bound by the chain of segments and many by the SIMDs; fill and
 // drain cost a walk down the longest query.  Measured / estimated, us: 1 x
 // 2,000 vs 100,000 2,062 / 2,086, 512 x 1,000 vs 20,000 1,223 / 1,090, 512 x
 // 250 vs 20,000 531 / 450.  Checkpoints cost it a quarter.
 //
-// Row-owning tiles: a step takes 0.05 + 0.010 T + 0.0069 R T us with DPP
-// exchange and 0.09 + 0.004 T + 0.0080 R T us through LDS with two wavefronts
-// per SIMD, about 8 % less with one, proportionally more with more; steps per
+// Row-owning tiles: a step takes 0.03 + 0.010 T + 0.0069 R T us with DPP
+// exchange and 0.07 + 0.004 T + 0.0080 R T us through LDS, and its share of a
+// barrier interval of KS steps, 0.15 us, with two wavefronts per SIMD, about
+// 8 % less with one, proportionally more with more; steps per
 // pass are the tiles of the reference and the fill (each lane lags its
 // neighbour by one step, each wavefront the one before by KS more).  512 x
-// 2,000 vs 100,000, (8,8,4,16) DPP: 7,198 / 7,272; 512 x 1,000 vs 20,000,
-// (4,8,4,8): 1,013 / 970.  A barrier interval with checkpoints costs 0.25 +
+// 2,000 vs 100,000, (8,8,4,16) DPP: 7,198 / 7,135; 512 x 1,000 vs 20,000,
+// (4,8,4,8): 1,013 / 966.  A barrier interval with checkpoints costs 0.35 +
 // 0.1 R us more.
 double variant_cost(const Variant& v, const BatchShape& s, int64_t ref_len, int32_t flags,
                     int cus) {
@@ -243,7 +242,7 @@ double variant_cost(const Variant& v, const BatchShape& s, int64_t ref_len, int3
   if (v.cols) {
     const bool wide = v.cols > kCkptQuantum;
     const double step = wide ? 0.275 : 0.165, shared = wide ? 0.20 : 0.09;
-    const double hop = wide ? 29.0 : 18.0;
+    const double hop = wide ? 27.0 : 17.5;
     const double nseg = (double)((ref_len + 64 * v.cols - 1) / (64 * v.cols));
     const double drain = (s.nmax + 63.0) * step;
     const double chain = (nseg - 1) * hop + drain;
@@ -280,12 +279,12 @@ double variant_cost(const Variant& v, const BatchShape& s, int64_t ref_len, int3
   }
   const double side = std::min<double>(fit, std::ceil((double)s.batch / cus));
   const double busy = std::max(1.0, side * waves / std::max(1.0, passes) / 4.0);
-  const double two = v.XL ? 0.09 + 0.004 * v.T + 0.0080 * v.R * v.T
-                          : 0.05 + 0.010 * v.T + 0.0069 * v.R * v.T;
+  const double two = 0.15 / v.KS + (v.XL ? 0.07 + 0.004 * v.T + 0.0080 * v.R * v.T
+                                         : 0.03 + 0.010 * v.T + 0.0069 * v.R * v.T);
   const double step = busy <= 2.0 ? two * (0.92 + 0.08 * (busy - 1.0)) : two * busy / 2.0;
   const double rounds = passes / (cus * side);
   double t = std::max(maxpass, rounds > 1.0 ? 1.05 * rounds : 1.0) * steps * step;
-  if (ck) t += std::max(maxpass, rounds) * steps / v.KS * (0.25 + 0.1 * v.R);
+  if (ck) t += std::max(maxpass, rounds) * steps / v.KS * (0.35 + 0.1 * v.R);
   return t + (persistent ? 8.0 : 0.0);
 }
 
@@ -878,7 +877,6 @@ int sdtw_forward_u8(const float* queries, const int32_t* h_query_lens, const int
   uint8_t* qcodes = reinterpret_cast<uint8_t*>(ws + L.qcodes);
   uint8_t* rcodes = reinterpret_cast<uint8_t*>(ws + L.rcodes);
   float2* part = reinterpret_cast<float2*>(ws + L.part);
-  sdtw::QBook* book = reinterpret_cast<sdtw::QBook*>(ws + L.book);
   {
     void* args[] = {(void*)&reference, (void*)&ref_len, (void*)&part};
     int rc = launch(reinterpret_cast<const void*>(&sdtw::sdtw_u8_minmax_kernel), dim3(L.nparts),
@@ -887,21 +885,13 @@ int sdtw_forward_u8(const float* queries, const int32_t* h_query_lens, const int
   }
   {
     int nparts = L.nparts;
-    void* args[] = {(void*)&part, (void*)&nparts, (void*)&book, (void*)&codebook};
-    int rc = launch(reinterpret_cast<const void*>(&sdtw::sdtw_u8_book_kernel), dim3(1),
-                    dim3(sdtw::kQThreads), args, stream);
-    if (rc != SDTW_OK) return rc;
-  }
-  const struct { const float* x; int64_t n; uint8_t* c; } enc[2] = {
-      {queries, total, qcodes}, {reference, ref_len, rcodes}};
-  for (const auto& e : enc) {
-    const float* x = e.x;
-    int64_t n = e.n;
-    uint8_t* c = e.c;
-    const int grid = (int)std::min<int64_t>((n + sdtw::kQThreads - 1) / sdtw::kQThreads, 8192);
-    void* args[] = {(void*)&x, (void*)&n, (void*)&book, (void*)&c};
-    int rc = launch(reinterpret_cast<const void*>(&sdtw::sdtw_u8_encode_kernel), dim3(grid),
-                    dim3(sdtw::kQThreads), args, stream);
+    int64_t nq = total, nr = ref_len;
+    const int grid = (int)std::min<int64_t>((nq + nr + sdtw::kQThreads - 1) / sdtw::kQThreads,
+                                            4096);
+    void* args[] = {(void*)&part, (void*)&nparts, (void*)&codebook, (void*)&queries, (void*)&nq,
+                    (void*)&qcodes, (void*)&reference, (void*)&nr, (void*)&rcodes};
+    const int rc = launch(reinterpret_cast<const void*>(&sdtw::sdtw_u8_encode_kernel), dim3(grid),
+                          dim3(sdtw::kQThreads), args, stream);
     if (rc != SDTW_OK) return rc;
   }
   // The DP itself: the plain forward over the codes (one byte per element).

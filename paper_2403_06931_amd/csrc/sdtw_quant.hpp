@@ -24,11 +24,6 @@ constexpr int kQThreads = 256;
 constexpr int kQPer = 16;                        // elements per thread, min/max pass
 constexpr int kQChunk = kQThreads * kQPer;       // elements per workgroup
 
-struct QBook {
-  float lo, hi;
-  double scale;
-};
-
 __device__ __forceinline__ void minmax_block(float& mn, float& mx, float* smin, float* smax) {
 #pragma unroll
   for (int d = kWave / 2; d > 0; d >>= 1) {
@@ -71,11 +66,15 @@ __global__ __launch_bounds__(kQThreads) void sdtw_u8_minmax_kernel(const float* 
   if (threadIdx.x == 0) part[blockIdx.x] = make_float2(mn, mx);
 }
 
-// The codebook from the chunk extremes.  One workgroup.
-__global__ __launch_bounds__(kQThreads) void sdtw_u8_book_kernel(const float2* __restrict__ part,
-                                                                int nparts,
-                                                                QBook* __restrict__ book,
-                                                                float* __restrict__ out) {
+// Codes of the packed queries and of the reference in one launch.  Every
+// workgroup forms the codebook from the chunk extremes itself (a few hundred
+// values; minimum and maximum depend on no order), which costs less than a
+// launch of its own; workgroup 0 also stores it.  Grid-stride over the
+// elements of both arrays.
+__global__ __launch_bounds__(kQThreads) void sdtw_u8_encode_kernel(
+    const float2* __restrict__ part, int nparts, float* __restrict__ out,
+    const float* __restrict__ q, int64_t nq, uint8_t* __restrict__ qcodes,
+    const float* __restrict__ r, int64_t nr, uint8_t* __restrict__ rcodes) {
   __shared__ float smin[kQThreads / kWave], smax[kQThreads / kWave];
   float mn = inf_f32(), mx = -inf_f32();
   for (int i = threadIdx.x; i < nparts; i += kQThreads) {
@@ -83,29 +82,22 @@ __global__ __launch_bounds__(kQThreads) void sdtw_u8_book_kernel(const float2* _
     mx = __builtin_fmaxf(mx, part[i].y);
   }
   minmax_block(mn, mx, smin, smax);
-  if (threadIdx.x == 0) {
-    const float lo = __builtin_fmaxf(mn, -kU8Clip);
-    const float hi = __builtin_fminf(mx, kU8Clip);
-    book->lo = lo;
-    book->hi = hi;
-    book->scale = hi > lo ? 255.0 / ((double)hi - (double)lo) : 0.0;
-    out[0] = lo;
-    out[1] = hi;
+  const float blo = __builtin_fmaxf(mn, -kU8Clip);
+  const float bhi = __builtin_fminf(mx, kU8Clip);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    out[0] = blo;
+    out[1] = bhi;
   }
-}
-
-// Codes of n packed values.  Grid-stride over elements.
-__global__ __launch_bounds__(kQThreads) void sdtw_u8_encode_kernel(const float* __restrict__ x,
-                                                                  int64_t n,
-                                                                  const QBook* __restrict__ book,
-                                                                  uint8_t* __restrict__ codes) {
-  const double lo = book->lo;
-  const double scale = book->scale;
+  const double lo = blo;
+  const double scale = bhi > blo ? 255.0 / ((double)bhi - (double)blo) : 0.0;
   const int64_t stride = (int64_t)gridDim.x * kQThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kQThreads + threadIdx.x; i < n; i += stride) {
-    double v = __builtin_rint(((double)x[i] - lo) * scale);
+  for (int64_t i = (int64_t)blockIdx.x * kQThreads + threadIdx.x; i < nq + nr; i += stride) {
+    const bool query = i < nq;
+    const float x = query ? q[i] : r[i - nq];
+    double v = __builtin_rint(((double)x - lo) * scale);
     v = v < 0.0 ? 0.0 : (v > 255.0 ? 255.0 : v);
-    codes[i] = (uint8_t)(int)v;
+    const uint8_t c = (uint8_t)(int)v;
+    if (query) qcodes[i] = c; else rcodes[i - nq] = c;
   }
 }
 
