@@ -84,20 +84,27 @@ __device__ __forceinline__ unsigned long long edge_get(const unsigned long long*
   return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// LDS of one wavefront: the rows' left edge and query value for lane 0 (two
-// groups in turn), every lane's right-most value over one group, and the
-// right-most column handed to the next wavefront: a ring of rows and, counted
-// over all items, the rows put into it and the rows read from it.
+// LDS of one wavefront: the rows' query values and, where the left edge comes
+// from global memory, the edge, for lane 0 (two groups in turn); every lane's
+// right-most value over one group (read for checkpoint columns; without
+// checkpoints nobody reads it, but one store of all lanes costs less than a
+// branch around lane 63's); and the ring that lane 63's goes to instead, from
+// where its column leaves for the next wavefront or for global memory, with
+// the rows put into it and read from it, counted over all items (an item's
+// rows start at a multiple of kColsRows, so a reader's group never wraps).
 constexpr int kColsWaves = kColsThreads / kWave;
 constexpr int kColsRing = 128;
+constexpr int kColsOut = kColsRows + 1;         // words per lane of `out` (odd: no conflicts)
 constexpr int kColsTickets = 4;
 
 template <typename V>
-struct ColsLds {
-  V in[2][kColsRows][2];
-  V out[kColsRows][kWave];
+struct alignas(16) ColsLds {
+  V q[2][kColsRows];
+  V edge[2][kColsRows];
   V ring[kColsRing];
+  V out[kWave * kColsOut];
   uint32_t put, got;
+  uint32_t pad[2];
 };
 
 // Items handed from wavefront 0 to the others: slot k % kColsTickets carries
@@ -142,6 +149,7 @@ struct ColsItem {
   unsigned long long* edge;     // the query's words
   bool from_lds, to_lds;        // the neighbouring segments are this workgroup's
   uint32_t in_base, out_base;   // rows of earlier items in the two rings
+  uint32_t got;                 // rows known to have left the wavefront's own ring
   int ck_stride, ck_first;      // checkpoint columns: every ck_stride-th lane from ck_first on
   int ck_k;                     // checkpoint (1..n_ckpt) of lane ck_first
 };
@@ -170,39 +178,41 @@ struct ColsStage {
     }
   }
   // `prev`: LDS of the wavefront before this one
-  __device__ __forceinline__ void commit(const ColsItem& I, ColsLds<V>& m, ColsLds<V>* prev,
-                                         int g0) {
-    V left = Val<V>::inf();
+  __device__ __forceinline__ void commit(const ColsItem& I, ColsLds<V>& m,
+                                         const ColsLds<V>* prev, int g0) {
+    const int buf = (g0 / kColsRows) & 1;
+    if (I.lane < kColsRows)
+      m.q[buf][I.lane] = Val<V>::N > 1 ? Val<V>::query(q, q2) : Val<V>::query(q, In(0));
     if (I.from_lds) {
       const int last = g0 + kColsRows < I.n ? g0 + kColsRows : I.n;
       if (last > g0) {
         while ((int32_t)(lds_get(&prev->put) - (I.in_base + (uint32_t)last)) < 0)
           __builtin_amdgcn_s_sleep(1);
-        left = prev->ring[(I.in_base + (uint32_t)(g0 + I.lane)) & (kColsRing - 1)];
-        lds_put(&prev->got, I.in_base + (uint32_t)last);
       }
-    } else if (I.seg > 0) {
-      const bool need = mine(I, g0);
-      while (__ballot(need && (uint32_t)(word >> 32) != (uint32_t)(I.seg - 1)) != 0) {
-        __builtin_amdgcn_s_sleep(2);
-        if (need) word = edge_get(I.edge + g0 + I.lane);
+    } else {
+      V left = Val<V>::inf();
+      if (I.seg > 0) {
+        const bool need = mine(I, g0);
+        while (__ballot(need && (uint32_t)(word >> 32) != (uint32_t)(I.seg - 1)) != 0) {
+          __builtin_amdgcn_s_sleep(2);
+          if (need) word = edge_get(I.edge + g0 + I.lane);
+        }
+        left = __builtin_bit_cast(V, (uint32_t)word);
       }
-      left = __builtin_bit_cast(V, (uint32_t)word);
-    }
-    if (I.lane < kColsRows) {
-      V(&at)[2] = m.in[(g0 / kColsRows) & 1][I.lane];
-      at[0] = left;
-      at[1] = Val<V>::N > 1 ? Val<V>::query(q, q2) : Val<V>::query(q, In(0));
+      if (I.lane < kColsRows) m.edge[buf][I.lane] = left;
     }
   }
 };
 
-// State of a lane: its columns' reference values and the DP row above the
-// next one, the left neighbour's value on that row (the diagonal) and the
-// query value of the row before.
+// State of a lane: its columns' reference values, the DP row above the next
+// one, the left neighbour's value on that row (the diagonal) and the query
+// value of the row before.  Steps read one of two rows and write the other
+// (even steps read d[0]), so that a step some lanes sit out needs no copies:
+// before row 1 both rows are row 0, and behind row n a lane's last row stays
+// where it was written.
 template <int C, typename V>
 struct ColsLane {
-  V rv[C], d[C];
+  V rv[C], d[2][C];
   V shp, qv;
   float tau;
 };
@@ -214,79 +224,102 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int C, int KIND, bool ROWCK, bool MASKED, typename V>
 __device__ __forceinline__ void cols_group(const ColsParams& p, const ColsItem& I,
-                                           ColsLane<C, V>& L, ColsLds<V>& m, int g0) {
-  V in[kColsRows][2];
-  const V(&src)[kColsRows][2] = m.in[(g0 / kColsRows) & 1];
+                                           ColsLane<C, V>& L, ColsLds<V>& m, ColsLds<V>* prev,
+                                           int g0) {
+  // (16-byte aligned, see ColsLds)
+  const V* esrc = I.from_lds ? prev->ring + ((I.in_base + (uint32_t)g0) & (kColsRing - 1))
+                             : m.edge[(g0 / kColsRows) & 1];
+  V edge[kColsRows], query[kColsRows];
+  tile_load<kColsRows, 4>(edge, esrc);
+  tile_load<kColsRows, 4>(query, m.q[(g0 / kColsRows) & 1]);
+  // lane 63's row g0 - 63 + s goes to ring place g0 - 63 + s of the item: one
+  // behind a multiple of kColsRows, so the last step's may wrap.  (Before row
+  // 0, and in a query's last segment, it has nothing to hand over, and the
+  // place may hold an earlier item's row that is still to be read.)
+  const uint32_t at = I.out_base + (uint32_t)(g0 - (kWave - 1));
+  const bool gives = I.lane == kWave - 1 && I.seg + 1 < I.nseg;
+  V* own = m.out + I.lane * kColsOut;
+  V* put = gives && g0 >= kWave ? m.ring + (at & (kColsRing - 1)) : own;
+  V* put_last = gives && g0 + kColsRows >= kWave
+                    ? m.ring + ((at + kColsRows - 1) & (kColsRing - 1)) : own + kColsRows - 1;
 #pragma unroll
   for (int s = 0; s < kColsRows; ++s) {
-    in[s][0] = src[s][0];
-    in[s][1] = src[s][1];
-  }
-#pragma unroll
-  for (int s = 0; s < kColsRows; ++s) {
-    V shc = in[s][0], q = in[s][1];
-    wave_shr1_pair(shc, L.d[C - 1], q, L.qv);
+    const V(&row)[C] = L.d[s & 1];
+    V(&next)[C] = L.d[(s & 1) ^ 1];
+    V shc = edge[s], q = query[s];
+    wave_shr1_pair(shc, row[C - 1], q, L.qv);
     L.qv = q;
     const int i = g0 + s - I.lane + 1;
     if (!MASKED || (i >= 1 && i <= I.n)) {
       V left = shc, diag = L.shp;
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const V up = L.d[c];
-        L.d[c] = Val<V>::template cell<KIND>(L.qv, L.rv[c], up, left, diag, L.tau);
-        diag = up;
-        left = L.d[c];
+        next[c] = Val<V>::template cell<KIND>(L.qv, L.rv[c], row[c], left, diag, L.tau);
+        diag = row[c];
+        left = next[c];
       }
       if constexpr (ROWCK) {
         if (i % kRowCkpt == 0 && i < I.n) {
           const int j = I.cs + I.lane * C;
-          float* row = p.rowck + (I.qoff / kRowCkpt + i / kRowCkpt - 1) * (int64_t)p.ref_len + j;
+          float* dst = p.rowck + (I.qoff / kRowCkpt + i / kRowCkpt - 1) * (int64_t)p.ref_len + j;
           if (j + C <= p.ref_len) {
 #pragma unroll
             for (int c = 0; c < C; c += 4)
-              __builtin_nontemporal_store(f32x4u{L.d[c], L.d[c + 1], L.d[c + 2], L.d[c + 3]},
-                                          reinterpret_cast<f32x4u*>(row + c));
+              __builtin_nontemporal_store(f32x4u{next[c], next[c + 1], next[c + 2], next[c + 3]},
+                                          reinterpret_cast<f32x4u*>(dst + c));
           } else {
             for (int c = 0; c < C; ++c)
-              if (j + c < p.ref_len) row[c] = L.d[c];
+              if (j + c < p.ref_len) dst[c] = next[c];
           }
         }
       }
     }
     L.shp = shc;
-    m.out[s][I.lane] = L.d[C - 1];
+    *(s + 1 < kColsRows ? put + s : put_last) = next[C - 1];
+  }
+  if (I.from_lds) {
+    const int last = g0 + kColsRows < I.n ? g0 + kColsRows : I.n;
+    if (last > g0) lds_put(&prev->got, I.in_base + (uint32_t)last);
   }
 }
 
 // After a group: hand over the rows lane 63 finished in it (rows g0 - 63 + s,
 // 0-based) to the next segment, and store the checkpoint columns.
 template <int C, bool CKPT, typename V>
-__device__ __forceinline__ void cols_publish(const ColsParams& p, const ColsItem& I,
-                                             ColsLds<V>& m, int g0) {
+__device__ __forceinline__ void cols_publish(const ColsParams& p, ColsItem& I, ColsLds<V>& m,
+                                             int g0) {
   const int s = I.lane & (kColsRows - 1);
-  const int row = g0 + s - (kWave - 1);
+  const int end = g0 + kColsRows - (kWave - 1);                // rows done, at most n
+  const int done = end < I.n ? end : I.n;
   if (I.to_lds) {
-    const int last = g0 + kColsRows - (kWave - 1);             // rows done, at most n
-    const int done = last < I.n ? last : I.n;
-    if (done > 0) {
-      while ((int32_t)(I.out_base + (uint32_t)done - lds_get(&m.got)) > kColsRing)
+    if (done > 0) lds_put(&m.put, I.out_base + (uint32_t)done);
+    // the rows of the group after this one must not overwrite rows not read
+    // yet (the first 63 places of an item belong to no row)
+    const uint32_t next = I.out_base + (uint32_t)(end + kColsRows);
+    if (end + kColsRows > 0 && (int32_t)(next - I.got) > kColsRing) {
+      for (;;) {
+        I.got = lds_get(&m.got);
+        if ((int32_t)(next - I.got) <= kColsRing) break;
         __builtin_amdgcn_s_sleep(1);
-      if (I.lane < kColsRows && row >= 0 && row < I.n)
-        m.ring[(I.out_base + (uint32_t)row) & (kColsRing - 1)] = m.out[s][kWave - 1];
-      lds_put(&m.put, I.out_base + (uint32_t)done);
+      }
     }
   } else if (I.seg + 1 < I.nseg) {
-    const uint32_t v = __builtin_bit_cast(uint32_t, m.out[s][kWave - 1]);
-    if (I.lane < kColsRows && row >= 0 && row < I.n) edge_put(I.edge + row, v, I.seg);
+    const int row = g0 + s - (kWave - 1);
+    const V v = m.ring[(I.out_base + (uint32_t)row) & (kColsRing - 1)];
+    if (I.lane < kColsRows && row >= 0 && row < I.n)
+      edge_put(I.edge + row, __builtin_bit_cast(uint32_t, v), I.seg);
   }
   if constexpr (CKPT) {
     int k = I.ck_k + I.lane / kColsRows;
     for (int l = I.ck_first + I.ck_stride * (I.lane / kColsRows);
          __ballot(l < kWave) != 0; l += I.ck_stride * (kWave / kColsRows)) {
       const int r = g0 + s - l;
-      if (l < kWave && k <= p.n_ckpt && r >= 0 && r < I.n)
-        __builtin_nontemporal_store(m.out[s][l],
-                                    p.ckpt + I.qoff * p.n_ckpt + (int64_t)(k - 1) * I.n + r);
+      if (l < kWave && k <= p.n_ckpt && r >= 0 && r < I.n) {
+        const V v = l == kWave - 1 && I.seg + 1 < I.nseg
+                        ? m.ring[(I.out_base + (uint32_t)r) & (kColsRing - 1)]
+                        : m.out[l * kColsOut + s];
+        __builtin_nontemporal_store(v, p.ckpt + I.qoff * p.n_ckpt + (int64_t)(k - 1) * I.n + r);
+      }
       k += kWave / kColsRows;
     }
   }
@@ -305,7 +338,7 @@ __device__ __forceinline__ void cols_item(const ColsParams& p, ColsItem& I, Cols
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     L.rv[c] = Val<V>::ref(j0 + c < p.ref_len ? r[j0 + c] : In(0));
-    L.d[c] = Val<V>::zero();                           // row 0
+    L.d[0][c] = L.d[1][c] = Val<V>::zero();            // row 0
   }
   L.shp = Val<V>::zero();
   L.qv = Val<V>::zero();
@@ -329,34 +362,48 @@ __device__ __forceinline__ void cols_item(const ColsParams& p, ColsItem& I, Cols
   st.commit(I, m, prev, 0);
   wave_fence();
   const int steps = I.n + kWave - 1;
-  for (int g0 = 0; g0 < steps; g0 += kColsRows) {
-    st.load(I, qa, qb, g0 + kColsRows);
-    const bool inside = g0 >= kWave && g0 + kColsRows <= I.n;  // every lane in rows 1..n
-    // (a multiple of kRowCkpt among rows g0 - 62 .. g0 + 8)
-    const bool rowck = CKPT && (g0 + kColsRows) / kRowCkpt != (g0 - kWave + 1) / kRowCkpt;
-    if (!inside) {
-      cols_group<C, KIND, CKPT, true, V>(p, I, L, m, g0);
-    } else if (rowck) {
-      if constexpr (CKPT) cols_group<C, KIND, true, false, V>(p, I, L, m, g0);
-    } else {
-      cols_group<C, KIND, false, false, V>(p, I, L, m, g0);
-    }
+  auto before = [&](int g0) { st.load(I, qa, qb, g0 + kColsRows); };
+  auto after = [&](int g0) {
     wave_fence();
     cols_publish<C, CKPT, V>(p, I, m, g0);
     st.commit(I, m, prev, g0 + kColsRows);
     wave_fence();
+  };
+  // lanes start, all lanes are in rows 1..n, lanes finish (three loops: where
+  // one loop held both forms of a step, its back edge copied both rows)
+  int g0 = 0;
+  for (; g0 < kWave; g0 += kColsRows) {
+    before(g0);
+    cols_group<C, KIND, CKPT, true, V>(p, I, L, m, prev, g0);
+    after(g0);
+  }
+  for (; g0 + kColsRows <= I.n; g0 += kColsRows) {
+    before(g0);
+    // (a multiple of kRowCkpt among rows g0 - 62 .. g0 + 8)
+    if (CKPT && (g0 + kColsRows) / kRowCkpt != (g0 - kWave + 1) / kRowCkpt) {
+      if constexpr (CKPT) cols_group<C, KIND, true, false, V>(p, I, L, m, prev, g0);
+    } else {
+      cols_group<C, KIND, false, false, V>(p, I, L, m, prev, g0);
+    }
+    after(g0);
+  }
+  for (; g0 < steps; g0 += kColsRows) {
+    before(g0);
+    cols_group<C, KIND, CKPT, true, V>(p, I, L, m, prev, g0);
+    after(g0);
   }
 
-  // row n: every lane's d[] holds its columns' values.  The segment's
+  // row n: lane l wrote its columns' values in step n - 1 + l.  The segment's
   // minimum is combined with the running one of the segments before (first
   // minimiser: a later segment wins only with a smaller value), which
   // travels like the edge; the last segment stores the result.
+  const bool odd = ((I.n - 1 + I.lane) & 1) != 0;
 #pragma unroll
   for (int h = 0; h < Val<V>::N; ++h) {
     ValIdx am{inf_f32(), 0};
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      const float v = Val<V>::half(L.d[c], h);
+      const float v = odd ? Val<V>::half(L.d[0][c], h) : Val<V>::half(L.d[1][c], h);
       if (j0 + c < p.ref_len && v < am.v) am = ValIdx{v, j0 + c};
     }
     am = wave_argmin(am);
@@ -409,7 +456,7 @@ __global__ __launch_bounds__(kColsThreads) void sdtw_cols_kernel(const ColsParam
   const bool alone = p.queue == nullptr;
   const int64_t groups = alone ? 1 : (p.nseg + kColsWaves - 1) / kColsWaves;
   const int64_t items = (int64_t)p.units * groups;
-  uint32_t in_base = 0, out_base = 0;
+  uint32_t in_base = 0, out_base = 0, got = 0;
   for (uint32_t k = 0;; ++k) {
     int64_t item;
     if (alone) {
@@ -442,6 +489,7 @@ __global__ __launch_bounds__(kColsThreads) void sdtw_cols_kernel(const ColsParam
     I.to_lds = !alone && w + 1 < kColsWaves && I.seg + 1 < p.nseg;
     I.in_base = in_base;
     I.out_base = out_base;
+    I.got = got;
     if (p.offsets != nullptr) {
       I.qoff = uniform64(p.offsets[I.b]);
     } else {
@@ -452,8 +500,14 @@ __global__ __launch_bounds__(kColsThreads) void sdtw_cols_kernel(const ColsParam
     }
     I.edge = p.edges + I.qoff + kColsExtra * (int64_t)I.b;
     cols_item<C, KIND, CKPT, V>(p, I, mem[w], w > 0 ? &mem[w - 1] : nullptr);
-    if (I.from_lds) in_base += (uint32_t)I.n;
-    if (I.to_lds) out_base += (uint32_t)I.n;
+    // (both sides of a ring count the rows rounded up to whole groups)
+    const uint32_t rows = (uint32_t)(I.n + kColsRows - 1) / kColsRows * kColsRows;
+    if (I.from_lds) {
+      in_base += rows;
+      lds_put(&mem[w - 1].got, in_base);
+    }
+    if (I.to_lds) out_base += rows;
+    got = I.got;
   }
 }
 
