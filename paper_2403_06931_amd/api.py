@@ -38,18 +38,20 @@ def _host_lens(lens) -> np.ndarray:
     return a
 
 
-def _hp(a: np.ndarray):
-    return ctypes.c_void_p(a.ctypes.data)
+# Addresses go to the library as plain integers (its functions declare their
+# pointer arguments, so ctypes converts them itself).
+def _hp(a: np.ndarray) -> int:
+    return a.ctypes.data
 
 
-def _dp(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(t.data_ptr() if t is not None else 0)
+def _dp(t: Optional[torch.Tensor]) -> int:
+    return t.data_ptr() if t is not None else 0
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _check(name: str, t, dtype, numel: Optional[int] = None,
@@ -109,12 +111,25 @@ def _check_batch(h: np.ndarray, queries, query_lens, reference=None,
                  qname: str = "queries", lname: str = "query_lens") -> None:
     if h.size < 1:
         raise ValueError("the batch must hold at least one query")
-    _check(qname, queries, torch.float32, numel=int(h.astype(np.int64).sum()))
+    _check(qname, queries, torch.float32, numel=int(np.add.reduce(h, dtype=np.int64)))
     _check(lname, query_lens, torch.int32, numel=h.size)
     if reference is not None:
         _check("reference", reference, torch.float32)
         if reference.numel() < 1:
             raise ValueError("reference must hold at least one value")
+
+
+def _forward_plan(hp: int, b: int, ref_len: int, flags: int, variant: int) -> Tuple[int, int]:
+    """(variant, workspace bytes) of a forward call; the library's choice is
+    asked for once and passed on, as every library call given -1 would make
+    it again."""
+    variant = int(variant)
+    if variant == -1:
+        variant = _lib.lib.sdtw_default_variant(hp, b, ref_len, flags)
+    need = _lib.lib.sdtw_forward_workspace_bytes(hp, b, ref_len, flags, variant)
+    if need == 0:
+        raise SdtwError(_lib.SDTW_ERR_INVALID_ARG, "sdtw_forward_workspace_bytes")
+    return variant, need
 
 
 def workspace(nbytes: int, device) -> torch.Tensor:
@@ -212,14 +227,13 @@ def sdtw_forward(queries: torch.Tensor, h_query_lens, query_lens: torch.Tensor,
     dev = queries.device
     cost = _new(cost, torch.float32, b, dev)
     end_pos = _new(end_pos, torch.int64, b, dev)
-    need = sdtw_forward_workspace_bytes(h, reference.numel(), flags, variant)
-    if need == 0:
-        raise SdtwError(_lib.SDTW_ERR_INVALID_ARG, "sdtw_forward_workspace_bytes")
+    hp, m, flags = _hp(h), reference.numel(), int(flags)
+    variant, need = _forward_plan(hp, b, m, flags, variant)
     workspace_buf = _workspace_arg(workspace_buf, need, dev)
     st = _lib.lib.sdtw_forward(
-        _dp(queries), _hp(h), _dp(query_lens), b, _dp(reference), reference.numel(),
-        int(cost_kind), _dp(cost), _dp(end_pos), _dp(ckpt), int(ckpt_every), int(variant),
-        int(flags), _dp(workspace_buf), workspace_buf.numel(), _stream(stream))
+        _dp(queries), hp, _dp(query_lens), b, _dp(reference), m,
+        int(cost_kind), _dp(cost), _dp(end_pos), _dp(ckpt), int(ckpt_every), variant,
+        flags, _dp(workspace_buf), workspace_buf.numel(), _stream(stream))
     check(st, "sdtw_forward")
     return cost, end_pos
 
@@ -272,13 +286,12 @@ def sdtw_forward_pruned(queries: torch.Tensor, h_query_lens, query_lens: torch.T
     dev = queries.device
     cost = _new(cost, torch.float32, b, dev)
     end_pos = _new(end_pos, torch.int64, b, dev)
-    need = sdtw_forward_workspace_bytes(h, reference.numel(), flags, variant)
-    if need == 0:
-        raise SdtwError(_lib.SDTW_ERR_INVALID_ARG, "sdtw_forward_workspace_bytes")
+    hp, m, flags = _hp(h), reference.numel(), int(flags)
+    variant, need = _forward_plan(hp, b, m, flags, variant)
     workspace_buf = _workspace_arg(workspace_buf, need, dev)
     st = _lib.lib.sdtw_forward_pruned(
-        _dp(queries), _hp(h), _dp(query_lens), b, _dp(reference), reference.numel(),
-        float(prune_tau), _dp(cost), _dp(end_pos), int(variant), int(flags),
+        _dp(queries), hp, _dp(query_lens), b, _dp(reference), m,
+        float(prune_tau), _dp(cost), _dp(end_pos), variant, flags,
         _dp(workspace_buf), workspace_buf.numel(), _stream(stream))
     check(st, "sdtw_forward_pruned")
     return cost, end_pos
