@@ -36,7 +36,8 @@
  *     failure returns SDTW_ERR_HIP.  Faults inside kernels surface at the
  *     caller's next synchronisation.
  *   - Inputs containing NaN or infinity give unspecified results.
- *   - Concurrent calls that share a workspace race; use one workspace per
+ *   - Concurrent calls that share a workspace race (and may not end: the
+ *     column-owning forward waits on words in it); use one workspace per
  *     stream.
  */
 #ifndef SDTW_H
@@ -192,11 +193,15 @@ SDTW_API int sdtw_forward(const float *queries, const int32_t *h_query_lens,
  * frees nothing.  Each GPU the library runs on holds its own array until the
  * process ends.
  *
- *   - With variant -1 the library chooses among the variants whose workspace
- *     fits the array.  A batch whose sdtw_forward_workspace_bytes(..., flags,
+ *   - With variant -1 the library chooses among the variants that run in the
+ *     array: those whose workspace fits it, except the column-owning ones
+ *     (sdtw_variant_info) where they need edge words, i.e. with a reference
+ *     of more than 1,024 columns: their wavefronts wait for values that
+ *     travel through the workspace, so it must belong to one call.  Such a
+ *     variant given explicitly is rejected with SDTW_ERR_WORKSPACE, and so is
+ *     a batch whose sdtw_forward_workspace_bytes(..., flags,
  *     variant) exceeds SDTW_NOALLOC_SCRATCH_BYTES for the given variant, or
- *     for every variant, is rejected with SDTW_ERR_WORKSPACE
- *     before anything is enqueued.  That covers any batch of up to about a
+ *     for every variant; nothing is enqueued then.  That covers any batch of up to about a
  *     million queries that fit in one row pass of the tile, plus
  *     SDTW_NOALLOC_SCRATCH_BYTES / (4 * ref_len) row-buffer slots for
  *     longer queries (sdtw_forward_workspace_bytes describes the slots).

@@ -327,10 +327,19 @@ FwdLayout fwd_layout_of(const Variant& v, const int32_t* h_lens, int32_t batch, 
                     fwd_edge_words(v, total, batch, ref_len));
 }
 
-// The variant with the smallest estimate, among those whose workspace is at
-// most max_bytes if any is (callers that cannot give more).
+// Whether a launch fits the library's own array, which calls that a caller
+// failed to serialise share: by size, and without edge words, which the
+// wavefronts of a launch wait on (a second launch that resets them could
+// leave a wait without an end; in every other form sharing only spoils
+// values).
+bool fits_scratch(const FwdLayout& L, int64_t edge_words) {
+  return edge_words == 0 && L.total <= SDTW_NOALLOC_SCRATCH_BYTES;
+}
+
+// The variant with the smallest estimate; with `scratch`, among those that
+// run in the library's own array, if any does.
 int pick_variant(const int32_t* h_lens, int32_t batch, int64_t ref_len, int32_t flags, int cus,
-                 size_t max_bytes = SIZE_MAX) {
+                 bool scratch = false) {
   const BatchShape s = batch_shape(h_lens, batch);
   int best = -1, best_any = 0;
   double best_cost = 0, best_any_cost = 0;
@@ -341,8 +350,8 @@ int pick_variant(const int32_t* h_lens, int32_t batch, int64_t ref_len, int32_t 
       best_any = i;
       best_any_cost = c;
     }
-    if (max_bytes != SIZE_MAX &&
-        fwd_layout_of(v, h_lens, batch, s.total, ref_len, flags, cus).total > max_bytes)
+    if (scratch && !fits_scratch(fwd_layout_of(v, h_lens, batch, s.total, ref_len, flags, cus),
+                                 fwd_edge_words(v, s.total, batch, ref_len)))
       continue;
     if (best < 0 || c < best_cost) {
       best = i;
@@ -722,18 +731,16 @@ int forward_impl(const float* queries, const int32_t* h_query_lens, const int32_
   const int cus = device_cus();
   const int vid = variant_id >= 0 ? variant_id
                                   : pick_variant(h_query_lens, batch, ref_len, flags, cus,
-                                                 use_scratch ? SDTW_NOALLOC_SCRATCH_BYTES
-                                                             : SIZE_MAX);
+                                                 use_scratch);
   const Variant& v = variant(vid);
   // the uint8-code kernel indexes the row buffer by query
   const int64_t slots = cost_kind == kU8Codes && !v.cols ? batch
                                               : fwd_slots(v, h_query_lens, batch, flags, cus);
-  const FwdLayout L =
-      fwd_layout(batch, ref_len, flags, slots, fwd_edge_words(v, total, batch, ref_len));
+  const int64_t edge_words = fwd_edge_words(v, total, batch, ref_len);
+  const FwdLayout L = fwd_layout(batch, ref_len, flags, slots, edge_words);
   if (use_scratch) {
-    // the library's own array (256-byte aligned), checked against its size
-    // before any HIP call
-    if (L.total > SDTW_NOALLOC_SCRATCH_BYTES) return SDTW_ERR_WORKSPACE;
+    // the library's own array (256-byte aligned), checked before any HIP call
+    if (!fits_scratch(L, edge_words)) return SDTW_ERR_WORKSPACE;
     workspace = scratch_address();
     if (workspace == nullptr) return SDTW_ERR_HIP;
   } else if (workspace_bytes < L.total) {
