@@ -58,15 +58,16 @@ struct Val<f16x2> {
   // The two queries' values, rounded to binary16.  One that rounds to an
   // infinity makes its query's every path cost +inf (no reference value is
   // at a finite distance); it is replaced by 0 here and the query's result
-  // set when it is stored (infinite).
+  // set when it is stored (infinite).  A NaN in an input counts as an
+  // infinity, so that it stays in its row or column.
   __device__ static _Float16 finite(float a) {
     return infinite(a) ? (_Float16)0.0f : (_Float16)a;
   }
-  __device__ static bool infinite(float a) { return __builtin_fabsf(a) >= 65520.0f; }
+  __device__ static bool infinite(float a) { return !(__builtin_fabsf(a) < 65520.0f); }
   __device__ static f16x2 query(float a, float b) { return f16x2{finite(a), finite(b)}; }
   // one reference value for both halves
   __device__ static f16x2 ref(float r) {
-    const _Float16 h = (_Float16)r;
+    const _Float16 h = (_Float16)(r != r ? inf_f32() : r);
     return f16x2{h, h};
   }
   template <int KIND>
@@ -81,7 +82,7 @@ struct Val<f16x2> {
     }
   }
   // v_pk_minimum3_f16: one instruction for both halves.  It hands a NaN on,
-  // but none arises from inputs that are not NaN: query values are finite
+  // but none arises: query values are finite and reference values not NaN
   // (above), so a difference is never inf - inf, and DP values are never
   // negative.
   __device__ static f16x2 min3(f16x2 a, f16x2 b, f16x2 c) {

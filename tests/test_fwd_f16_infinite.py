@@ -3,7 +3,7 @@ references and both, on every variant.  A query holding one costs +inf with
 end position 0 (every path passes its row; the oracle's own minimum is not
 defined there, where the reference holds an infinity too: inf - inf is NaN);
 one in the reference only makes its column impassable, and the other queries
-agree with the oracle bit for bit."""
+agree with the oracle bit for bit.  A NaN acts as an infinity."""
 import numpy as np
 import pytest
 import torch
@@ -29,6 +29,7 @@ def test_infinite_values(kind, ref_len):
     r = rng.standard_normal(ref_len).astype(np.float32)
     r[[0, 7, ref_len - 1]] = 1e5, -1e5, 65520.0
     want_c, want_e = oracle.sdtw_f16(q, lens, r, kind)
+    r[7] = np.nan                          # as impassable as the infinity it replaces
     assert np.isfinite(want_c[[1, 2, 5]]).all()
     want_c[[0, 3, 6]] = np.inf
     want_e[[0, 3, 6]] = 0
